@@ -206,14 +206,16 @@ lb_status lb_status_flags(lb_handle *h, uint32_t *flags, int64_t *step);
 
 /* The fused step's launch configuration chosen by lb_init: steps per launch (1: one step per
  * launch; 2: two steps per launch, the post-collision rows of the first kept on chip for the
- * second, so that HBM holds only every other state), and that kernel's workgroup (strip)
- * width in lanes, rows per tile and number of workgroups.  An odd step count ends with one
- * single-step launch.  For lattices of 2^22 nodes or more the configuration is picked by
- * timing candidates on the caller's stream (smaller ones take two steps per launch); the
- * environment variables LBF_TILE="width,rows" (one step per launch) and
- * LBF_TILE2="width,rows" (two) pin a shape, LBF_STEPS_PER_LAUNCH=1 or 2 the kernel.
- * Handles with correlated noise take one step per launch.  The configuration changes the
- * schedule only: results are bitwise identical for every shape and either kernel.
+ * second, so that HBM holds only every other state; 4: small lattices in FP32), and that
+ * kernel's workgroup (strip) width in lanes, rows per tile and number of workgroups.  The rest of
+ * a step count takes single-step launches.  Lattices of fewer than 2^22 nodes take tiles 64
+ * columns wide with a lane per node, their steps per launch and height from the tile count; for
+ * larger ones the configuration is picked by timing candidates on the caller's stream.  The
+ * environment variables LBF_TILE="width,rows" (one step per launch) and LBF_TILE2="width,rows"
+ * (two) pin a shape of the strips that march down their rows, LBF_STEPS_PER_LAUNCH=1 or 2 their
+ * kernel, LBF_NODE_TILE="steps,rows" (1, 2 or 4; at most 16) the tiles with a lane per node.
+ * Handles with correlated noise take one or two steps per launch.  The configuration changes the
+ * schedule only: results are bitwise identical for every shape and kernel.
  * Host-only; any output pointer may be NULL. */
 lb_status lb_tuning(lb_handle *h, int32_t *strip_width, int32_t *rows_per_tile, int32_t *ntiles,
                     int32_t *steps_per_launch);

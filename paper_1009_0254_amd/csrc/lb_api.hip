@@ -62,6 +62,11 @@ constexpr int MAX_RED_BLOCKS = 1024;
 constexpr int GRAPH_STEPS = 32;   // steps per captured graph (even: buffers return to place)
 constexpr int MIN_BX = 64, MIN_H = 4;
 constexpr int CN_MAX = 8192;        // longest side with correlated noise
+// both population buffers below this: k_tile's stores stay in the 256 MB last-level cache
+// (us per step, 2048 x 400 FP32, 59 MB: 12.5 against 14.2 with the nontemporal policy; 2048^2,
+// 302 MB: one step per launch 65 against 61)
+constexpr size_t TILE_CACHED_BYTES = (size_t)224 << 20;
+constexpr int TILE_ONE_STEP_TY = 4;
 constexpr int SAMPLE_GRAPH_MAX = 256;   // longest sampling interval captured as one graph
 
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
@@ -276,6 +281,13 @@ struct lb_handle {
     Tile *tiles2_d = nullptr;
     int32_t *wgs2_d = nullptr;
     int nwg2 = 0, bx2 = 256, rows2 = 32, gmax2 = 1;
+    // a lane per node (k_tile): tns steps per launch (0: not used), then single steps; the shapes of
+    // the two, their tile counts and tables
+    int tns = 0;
+    struct NodeTiles {
+        int ns = 1, ty = 4, ntiles = 0;
+        Tile *table = nullptr;
+    } nt[2];   // tns steps; one step
     unsigned long long *tdev = nullptr;
     unsigned *flags = nullptr;
     double *partials = nullptr, *tot = nullptr, *rho_tmp = nullptr;
@@ -471,11 +483,109 @@ hipError_t step_pair(lb_handle *h, int par, int toff, hipStream_t s)
     return launch_step2(h->precision, a, s);
 }
 
-// `n` steps from buffer *par on stream s, time offsets toff.. (k_step2 for pairs when k = 2);
-// *par follows the state
+// k_tile's launch of ns steps in tiles of ty rows: nt[0] (tns steps) or nt[1] (single steps)
+lb_status set_node_tiles(lb_handle *h, int which, int ns, int ty)
+{
+    // what k_tile's variants, launch bounds and tile geometry allow
+    if (!(ns == 1 || ns == 2 || (ns == 4 && h->precision != LB_FP64 && h->cn_reps.empty())) || ty <= 4 * (ns - 1) ||
+        ty > TILE_MAX_TY)
+        return LB_EINVAL;
+    lb_handle::NodeTiles &q = h->nt[which];
+    q.ns = ns;
+    q.ty = ty;
+    q.table = which == 0 ? h->tiles_d : h->tiles2_d;   // lists that k_tile's handles do not use otherwise
+    std::vector<Tile> table;
+    long long n = 0;
+    for (const auto &d : h->reps) {
+        table.push_back(Tile{0, (int32_t)n, 0, 0});
+        n += tile_count(d.nx, d.ny, ns, ty);
+    }
+    q.ntiles = (int)n;
+    if (hipMemcpyAsync(q.table, table.data(), sizeof(Tile) * table.size(), hipMemcpyHostToDevice, h->stream) != hipSuccess ||
+        hipStreamSynchronize(h->stream) != hipSuccess)
+        return LB_EDEVICE;
+    return LB_OK;
+}
+
+// Steps per launch and tile height of k_tile.  A launch costs ~2 us before its first collision,
+// a step inside a launch the collisions of the rows that the tile loses at its edges.  While the
+// tiles of a launch find a CU each, the lost rows cost nothing: the lowest tiles for which that holds
+// are taken (a CU's fewer waves run faster), with four steps per launch for the smallest lattices
+// in FP32 and two otherwise (us per step, one replica, FP32: 128^2 4 x 16 rows 2.6, 2 x 6 2.9,
+// 1 x 4 4.0; 256^2 4 x 16 3.8, 2 x 10 3.4, 2 x 16 4.0, 1 x 4 4.2).  Beyond, FP32 takes two steps in the
+// tallest tiles (1500 x 1101: 2 x 16 21.3, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.5, 13.3 and
+// 13.5), and FP64, whose collision is longer than the launch, one (256^2: 1 x 4 5.7, 2 x 10 5.9; 512^2
+// 12.5 and 13.8; 2048 x 400 27.6 and 32.6).
+void node_tile_shape(const lb_handle *h, int *ns, int *ty)
+{
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
+        ncu = 256;
+    auto count = [&](int s, int y) {
+        long long n = 0;
+        for (const auto &d : h->reps) n += tile_count(d.nx, d.ny, s, y);
+        return n;
+    };
+    const bool fp64 = h->precision == LB_FP64;
+    *ns = 4;
+    *ty = TILE_MAX_TY;
+    if (!fp64 && h->cn_reps.empty() && count(4, TILE_MAX_TY) <= ncu) return;
+    *ns = 2;
+    for (*ty = 6; *ty < (fp64 ? 8 : TILE_MAX_TY); *ty += 2)
+        if (count(2, *ty) <= ncu) return;
+    if (!fp64) return;
+    *ns = 1;
+    *ty = TILE_ONE_STEP_TY;
+}
+
+// nt[which].ns steps from time t + toff, buffer par into buffer par ^ 1 (correlated noise first, a
+// plane a step)
+hipError_t step_tile(lb_handle *h, int which, int par, int toff, hipStream_t s)
+{
+    const lb_handle::NodeTiles &q = h->nt[which];
+    const int64_t plane = 2 * h->L.cn_nodes;
+    for (int j = 0; j < q.ns; ++j)
+        for (int r : h->cn_reps) {
+            void *xi = (char *)h->xi + (size_t)j * plane * elem_size(h->precision);
+            hipError_t e = launch_correlated_noise(h->precision, h->reps_d, h->reps[r], r, h->cn_a, h->cn_tw, xi,
+                                                   h->tdev, toff + j, s);
+            if (e != hipSuccess) return e;
+        }
+    TileLaunch a;
+    a.xi = h->cn_reps.empty() ? nullptr : h->xi;
+    a.xi_plane = plane;
+    a.fin = h->fbuf[par];
+    a.fout = h->fbuf[par ^ 1];
+    a.reps = h->reps_d;
+    a.table = q.table;
+    a.tdev = h->tdev;
+    a.flags = h->flags;
+    a.toff = toff;
+    a.nrep = h->n_rep;
+    a.ntiles = q.ntiles;
+    a.ns = q.ns;
+    a.ty = q.ty;
+    a.plain = h->precision == LB_FP32 ? 1 : 0;
+    a.cached = 18.0 * h->L.nodes * elem_size(h->precision) < (double)TILE_CACHED_BYTES ? 1 : 0;
+    return launch_tile(h->precision, a, s);
+}
+
+// `n` steps from buffer *par on stream s, time offsets toff.. (k_tile when tns, else k_step2 for
+// pairs when k = 2); *par follows the state
 hipError_t enqueue_steps(lb_handle *h, long long n, int *par, int toff, hipStream_t s)
 {
     long long k = 0;
+    if (h->tns) {
+        while (k < n) {
+            const int which = n - k >= h->tns ? 0 : 1;
+            hipError_t e = step_tile(h, which, *par, toff + (int)k, s);
+            if (e != hipSuccess) return e;
+            *par ^= 1;
+            k += h->nt[which].ns;
+        }
+        return hipSuccess;
+    }
     if (h->k == 2)
         for (; k + 2 <= n; k += 2) {
             hipError_t e = step_pair(h, *par, toff + (int)k, s);
@@ -625,7 +735,7 @@ lb_status autotune(lb_handle *h)
         max_nx = std::max(max_nx, d.nx);
     }
     // pinned shapes: LBF_TILE="width,rows" (one step per launch), LBF_TILE2="width,rows" (two);
-    // LBF_STEPS_PER_LAUNCH=1 or 2 forces the kernel
+    // LBF_STEPS_PER_LAUNCH=1 or 2 forces the kernel; LBF_NODE_TILE="steps,rows" takes k_tile
     auto pinned = [](const char *name, int minbx, int minh, int *bx, double *rows) {
         const char *env = getenv(name);
         return env && sscanf(env, "%d,%lf", bx, rows) == 2 && *bx >= minbx && *bx <= 512 && *bx % 64 == 0 &&
@@ -639,6 +749,16 @@ lb_status autotune(lb_handle *h)
     const bool pin2 = pinned("LBF_TILE2", STEP2_MIN_BX, STEP2_MIN_H, &pbx2, &prows2);
     if (!force_k) force_k = pin1 && !pin2 ? 1 : (pin2 && !pin1 ? 2 : 0);
 
+    int tns = 0, tty = 0;
+    const char *tile_env = getenv("LBF_NODE_TILE");
+    const bool pint = tile_env && sscanf(tile_env, "%d,%d", &tns, &tty) == 2;
+    if (pint || (h->L.nodes < (1ll << 22) && !pin1 && !pin2 && !force_k)) {
+        if (!pint) node_tile_shape(h, &tns, &tty);
+        lb_status st = set_node_tiles(h, 0, tns, tty);
+        if (st == LB_OK) st = set_node_tiles(h, 1, 1, TILE_ONE_STEP_TY);
+        if (st == LB_OK) h->tns = tns;
+        return st;
+    }
     int bx0 = 256;
     while (bx0 > MIN_BX && bx0 / 2 >= min_nx) bx0 /= 2;
     int bx20 = 256;
@@ -792,7 +912,7 @@ lb_status capture_graph(lb_handle *h, int par)
     }
     int p = par;
     if (enqueue_steps(h, GRAPH_STEPS, &p, 0, cs) != hipSuccess) st = LB_EDEVICE;
-    if (p != par) st = LB_EDEVICE;   // GRAPH_STEPS is a multiple of 4: the state returns to buffer par
+    if (p != par) st = LB_EDEVICE;   // an even number of launches of 1, 2 or 4 steps: the state returns to buffer par
     if (launch_advance_time(h->tdev, GRAPH_STEPS, cs) != hipSuccess) st = LB_EDEVICE;
     if (hipStreamEndCapture(cs, &g) != hipSuccess) st = LB_EDEVICE;
     if (st == LB_OK && hipGraphInstantiate(&h->graph[par], g, nullptr, nullptr, 0) != hipSuccess) st = LB_EDEVICE;
@@ -844,7 +964,11 @@ lb_status run_steps(lb_handle *h, long long nsteps)
 }
 
 // buffer parity change of `n` steps as enqueue_steps takes them
-int parity_of(const lb_handle *h, long long n) { return (int)((h->k == 2 ? n / 2 + (n & 1) : n) & 1); }
+int parity_of(const lb_handle *h, long long n)
+{
+    const long long k = h->tns ? h->tns : h->k;
+    return (int)((n / k + n % k) & 1);
+}
 
 }  // namespace
 
@@ -967,7 +1091,7 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
             return LB_EDEVICE;
         }
     }
-    if ((e = set_step2_lds_limit()) != hipSuccess) {
+    if ((e = set_step2_lds_limit()) != hipSuccess || (e = set_tile_lds_limit()) != hipSuccess) {
         delete h;
         return LB_EDEVICE;
     }
@@ -1162,6 +1286,13 @@ lb_status lb_tuning(lb_handle *h, int32_t *strip_width, int32_t *rows_per_tile, 
                     int32_t *steps_per_launch)
 {
     if (!h) return LB_EINVAL;
+    if (h->tns) {
+        if (strip_width) *strip_width = 64;
+        if (rows_per_tile) *rows_per_tile = h->nt[0].ty - 4 * (h->tns - 1);
+        if (ntiles) *ntiles = h->nt[0].ntiles;
+        if (steps_per_launch) *steps_per_launch = h->tns;
+        return LB_OK;
+    }
     if (strip_width) *strip_width = h->k == 2 ? h->bx2 : h->bx;
     if (rows_per_tile) *rows_per_tile = h->k == 2 ? h->rows2 : h->rows;
     if (ntiles) *ntiles = h->k == 2 ? h->nwg2 : h->ntiles;

@@ -29,14 +29,14 @@ template <> __device__ __forceinline__ double bld<double>(__amdgpu_buffer_rsrc_t
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
 }
 constexpr int CPOL_NT = 2;
-template <typename S> __device__ __forceinline__ void bst(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, S v);
-template <> __device__ __forceinline__ void bst<float>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, float v)
+template <typename S, bool CACHED = false>
+__device__ __forceinline__ void bst(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, S v)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)voff, (int)soff, CPOL_NT);
-}
-template <> __device__ __forceinline__ void bst<double>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, double v)
-{
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, (int)voff, (int)soff, CPOL_NT);
+    constexpr int cpol = CACHED ? 0 : CPOL_NT;
+    if constexpr (sizeof(S) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)voff, (int)soff, cpol);
+    else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, (int)voff, (int)soff, cpol);
 }
 
 template <typename R> __device__ __forceinline__ R frcp(R v);

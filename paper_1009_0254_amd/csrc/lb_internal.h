@@ -144,6 +144,32 @@ int step2_blocks_per_cu(int precision, bool plain, bool cn, int bx, int max_grou
 // allow k_step2 the dynamic LDS of its largest configuration (512 lanes in 8 groups)
 hipError_t set_step2_lds_limit();
 
+// Small and middle-sized lattices (lb_tile.hip): ns steps per launch (1, 2 or, in FP32
+// without correlated noise, 4), a lane per node, tiles of 64 columns and ty rows (the first step's; a step
+// more loses two at each edge).  table[r].x0 is the index of replica r's first tile (unused for
+// one replica); cached: 0 stores with the nontemporal policy.
+struct TileLaunch {
+    const void *xi;
+    int64_t xi_plane;
+    const void *fin;
+    void *fout;
+    const RepDesc *reps;
+    const Tile *table;
+    const unsigned long long *tdev;
+    unsigned *flags;
+    int32_t toff;
+    int32_t nrep, ntiles;
+    int32_t ns, ty;
+    int32_t plain, cached;
+};
+constexpr int TILE_MAX_TY = 16;
+hipError_t launch_tile(int precision, const TileLaunch &a, hipStream_t s);
+// LDS of a workgroup: at most 42 KB (FP32) or 84 KB (FP64)
+size_t tile_lds_bytes(int precision, int ns, int ty);
+// tiles of a replica
+long long tile_count(int nx, int ny, int ns, int ty);
+hipError_t set_tile_lds_limit();
+
 // launchers (lb_kernels.hip); all return hipSuccess or the launch error
 hipError_t launch_step(int precision, const StepLaunch &a, hipStream_t s);
 hipError_t launch_advance_time(unsigned long long *tdev, long long by, hipStream_t s);
