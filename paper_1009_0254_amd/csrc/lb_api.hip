@@ -512,10 +512,10 @@ lb_status set_node_tiles(lb_handle *h, int which, int ns, int ty)
 // tiles of a launch find a CU each, the lost rows cost nothing: the lowest tiles for which that holds
 // are taken (a CU's fewer waves run faster), with four steps per launch for the smallest lattices
 // in FP32 and two otherwise (us per step, one replica, FP32: 128^2 4 x 16 rows 2.6, 2 x 6 2.9,
-// 1 x 4 4.0; 256^2 4 x 16 3.8, 2 x 10 3.4, 2 x 16 4.0, 1 x 4 4.2).  Beyond, FP32 takes two steps in the
-// tallest tiles (1500 x 1101: 2 x 16 21.3, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.5, 13.3 and
-// 13.5), and FP64, whose collision is longer than the launch, one (256^2: 1 x 4 5.7, 2 x 10 5.9; 512^2
-// 12.5 and 13.8; 2048 x 400 27.6 and 32.6).
+// 1 x 4 4.0; 256^2 4 x 16 3.8, 2 x 10 3.4, 2 x 16 4.0, 1 x 4 4.2; FP64: 64^2 4 x 14 4.8, 2 x 6 3.6, 1 x 4
+// 4.8, 256^2 2 x 10 5.1, 1 x 4 5.3).  Beyond, the tallest tiles of which a CU holds two workgroups: 16
+// rows in FP32 (60 VGPRs; 1500 x 1101: 2 x 16 21.3, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.5, 13.3 and
+// 13.5), 12 in FP64 (80 VGPRs; 2048 x 400: 2 x 12 23.6, 2 x 16 28.4, 1 x 4 25.1; 512^2 11.4, 11.7, 11.4).
 void node_tile_shape(const lb_handle *h, int *ns, int *ty)
 {
     int dev = 0, ncu = 0;
@@ -532,11 +532,9 @@ void node_tile_shape(const lb_handle *h, int *ns, int *ty)
     *ty = TILE_MAX_TY;
     if (!fp64 && h->cn_reps.empty() && count(4, TILE_MAX_TY) <= ncu) return;
     *ns = 2;
-    for (*ty = 6; *ty < (fp64 ? 8 : TILE_MAX_TY); *ty += 2)
+    const int most = fp64 ? 12 : TILE_MAX_TY;
+    for (*ty = 6; *ty < most; *ty += 2)
         if (count(2, *ty) <= ncu) return;
-    if (!fp64) return;
-    *ns = 1;
-    *ty = TILE_ONE_STEP_TY;
 }
 
 // nt[which].ns steps from time t + toff, buffer par into buffer par ^ 1 (correlated noise first, a

@@ -41,7 +41,7 @@ __device__ __forceinline__ void bst(__amdgpu_buffer_rsrc_t r, unsigned voff, uns
 
 template <typename R> __device__ __forceinline__ R frcp(R v);
 template <> __device__ __forceinline__ float frcp<float>(float v) { return __builtin_amdgcn_rcpf(v); }
-template <> __device__ __forceinline__ double frcp<double>(double v) { return 1.0 / v; }
+template <> __device__ __forceinline__ double frcp<double>(double v) { return rcp64(v); }
 
 // a + b rounded once, never contracted with the product that formed a (the re-shift of plain
 // FP32 storage after the back-transform must round the same way in every kernel)
@@ -51,7 +51,15 @@ template <> __device__ __forceinline__ double add_rn<double>(double a, double b)
 
 template <typename R> __device__ __forceinline__ R fsqrt(R v);
 template <> __device__ __forceinline__ float fsqrt<float>(float v) { return __builtin_amdgcn_sqrtf(v); }
-template <> __device__ __forceinline__ double fsqrt<double>(double v) { return sqrt(v); }
+template <> __device__ __forceinline__ double fsqrt<double>(double v) { return sqrt64(v); }
+
+// the root of v > 0 and its reciprocal
+__device__ __forceinline__ void root_and_rcp(float v, float &r, float &ir)
+{
+    r = fsqrt<float>(v);
+    ir = frcp<float>(r);
+}
+__device__ __forceinline__ void root_and_rcp(double v, double &r, double &ir) { sqrt_rsqrt64(v, r, ir); }
 
 // density deviation rho - rho0 of nine pulled stored values (PLAIN: stored f_i, whose sum
 // includes rho0 = sum_i fbar_i), in one fixed summation order
@@ -169,7 +177,7 @@ __device__ __forceinline__ unsigned collide(R f[Q], R lap, R gx, R gy, const Con
         // correlated noise: modes 4 and 9 from the filtered fields, modes 5..8 white at rho0
         // (normals scaled by sqrt(3 kT rho0))
         R nu[6];
-        normals6s<R>(node, rep, t, k0, k1, c.sq0, nu);
+        normals6s<R>(node, rep, t, k0, k1, noise_scale<R>(c.kT3 * c.rho0, c.sq0), nu);
         s4 += xi4;
         s9 += xi9;
         s5 += c.l55 * nu[1];
@@ -190,11 +198,13 @@ __device__ __forceinline__ unsigned collide(R f[Q], R lap, R gx, R gy, const Con
         const R a49 = c.k49 * cs2 + vk.k49m;           // k49 (c_s^2 - 1/3)
         const R a99 = vk.k99x125 + c.k99n075 * cs2;    // k99 (5/4 - 3 c_s^2 / 4)
         R nu[6];
-        normals6s<R>(node, rep, t, k0, k1, fsqrt<R>(rr * c.kT3), nu);
+        const R var = rr * c.kT3;
+        normals6s<R>(node, rep, t, k0, k1, sizeof(R) == 8 ? var : fsqrt<R>(var), nu);
         R l44 = 0, l94 = 0;
         if (a44 > 0) {
-            l44 = fsqrt<R>(a44);
-            if (noise != 3) l94 = a49 * frcp<R>(l44);   // 3: the diagonal of Xi(0) only (Sec. IV)
+            R i44;
+            root_and_rcp(a44, l44, i44);
+            if (noise != 3) l94 = a49 * i44;   // 3: the diagonal of Xi(0) only (Sec. IV)
         } else if (a44 < 0) {
             st |= 1u;
         }

@@ -57,77 +57,139 @@ __device__ __forceinline__ void bits21(uint4 x, uint32_t b[6])
 }
 
 // Box-Muller on u = (b + 1/2) 2^-21 (exact in float and double)
+// ------------------------------------------------------------------ FP64 reciprocal and square root
+// The compiler's FP64 division and square root guard every argument (scaling, special cases), 11 and
+// about 17 instructions; the ranges here need less.  Both start from the hardware's ~2^-24 estimate:
+// Newton's iteration doubles the correct bits, and a last residual formed with fma rounds within
+// 0.51 ulp.  The host build takes the correctly rounded operations.
+
+// 1 / v; zero, infinite and NaN arguments as the division has them
+__host__ __device__ inline double rcp64(double v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double y = __builtin_amdgcn_rcp(v);
+    y = fma(fma(-v, y, 1.0), y, y);
+    y = fma(fma(-v, y, 1.0), y, y);
+    return __builtin_amdgcn_div_fixup(y, v, 1.0);
+#else
+    return 1.0 / v;
+#endif
+}
+
+// a / v for finite a and normal v whose quotient is normal
+__host__ __device__ inline double div64(double a, double v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double y = __builtin_amdgcn_rcp(v);
+    y = fma(fma(-v, y, 1.0), y, y);
+    const double q = a * y;
+    return fma(fma(-v, q, a), y, q);
+#else
+    return a / v;
+#endif
+}
+
+// sqrt(x) for finite x >= 0 (0 gives 0; below the normal range, where the root is under 1.5e-154,
+// only its size is kept), NaN for a NaN
+__host__ __device__ inline double sqrt64(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double y = __builtin_amdgcn_rsq(fmax(x, 0x1p-1022));
+    double g = x * y;
+    const double h = 0.5 * y;
+    g = fma(fma(-h, g, 0.5), g, g);
+    return fma(fma(-g, g, x), h, g);
+#else
+    return sqrt(x);
+#endif
+}
+
+// the same with the reciprocal of the root: r = sqrt(x), ir = 1 / r for normal x > 0
+__host__ __device__ inline void sqrt_rsqrt64(double x, double &r, double &ir)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(e, g, g);
+    h = fma(e, h, h);
+    r = fma(fma(-g, g, x), h, g);
+    const double i = h + h;
+    ir = fma(fma(-r, i, 1.0), i, i);
+#else
+    r = sqrt(x);
+    ir = 1.0 / r;
+#endif
+}
+
 // ------------------------------------------------------------------ FP64 ln u, sin and cos of 2 pi u
 // Box-Muller meets these only at u = (b + 1/2) 2^-21 with b a 21-bit integer, which admits exact
 // argument reductions and short series instead of the general-argument library routines.  The
-// operations are products, sums, explicit fma, one division and bit manipulation, all correctly
-// rounded, so a host build of these functions gives the same bits (checked there over every b
-// against long-double references).
+// series are least-maximum fits over the reduced ranges (Lawson's reweighted least squares in 80-bit
+// arithmetic, coefficients rounded to double), their own error below 2e-17 of the result.  The
+// operations are products, sums, explicit fma, one quotient and bit manipulation, so a host build of
+// these functions gives the same values (checked there over every b against long-double references).
 
 // ln u: u = (2 b + 1) 2^-22 (exact) = m 2^e with m in [sqrt(1/2), sqrt(2)), m - 1 exact; ln m =
-// 2 atanh(s), s = (m - 1) / (m + 1), |s| <= 0.1716, by its series to the s^19 term (truncation
-// below 3e-17 relative); e ln 2 with ln 2 = hi + lo, hi being ln 2 rounded to 40 significant
-// bits (so that e hi is exact for |e| <= 22) and lo the rest rounded to double.
+// 2 atanh(s), s = (m - 1) / (m + 1), |s| <= 0.1716: 2 s + 2 s^3 p(s^2) with p of degree 6; e ln 2
+// with ln 2 = hi + lo, hi being ln 2 rounded to 40 significant bits (so that e hi is exact for
+// |e| <= 22) and lo the rest rounded to double.
 __host__ __device__ inline double u21_ln(uint32_t b)
 {
     const double u = (double)(2u * b + 1u) * 0x1p-22;
     const unsigned long long bits = __builtin_bit_cast(unsigned long long, u);
-    int e = (int)((bits >> 52) & 0x7FFu) - 1023;
-    double m = __builtin_bit_cast(double, (bits & 0x000FFFFFFFFFFFFFull) | 0x3FF0000000000000ull);
-    if (m > 1.4142135623730951) {
-        m *= 0.5;
-        ++e;
-    }
+    // exponent and mantissa from the high word, the mantissa's bound at sqrt(2) cut to that word
+    const uint32_t hw = (uint32_t)(bits >> 32), up = (hw & 0xFFFFFu) > 0x6A09Eu ? 1u : 0u;
+    const int e = (int)(hw >> 20) - 1023 + (int)up;
+    const uint32_t mw = (hw & 0xFFFFFu) | (0x3FF00000u - (up << 20));
+    const double m = __builtin_bit_cast(double, ((unsigned long long)mw << 32) | (bits & 0xFFFFFFFFull));
     const double f = m - 1.0;
-    const double sv = f / (2.0 + f);
+    const double sv = div64(f, 2.0 + f);
     const double z = sv * sv;
-    double p = 1.0 / 19.0;
-    p = fma(p, z, 1.0 / 17.0);
-    p = fma(p, z, 1.0 / 15.0);
-    p = fma(p, z, 1.0 / 13.0);
-    p = fma(p, z, 1.0 / 11.0);
-    p = fma(p, z, 1.0 / 9.0);
-    p = fma(p, z, 1.0 / 7.0);
-    p = fma(p, z, 1.0 / 5.0);
-    p = fma(p, z, 1.0 / 3.0);
+    double p = 0x1.2f05742c2aeaep-4;
+    p = fma(p, z, 0x1.39a1b9258881cp-4);
+    p = fma(p, z, 0x1.74663ef8f8529p-4);
+    p = fma(p, z, 0x1.c71c5208f4cd4p-4);
+    p = fma(p, z, 0x1.24924941f1f1ap-3);
+    p = fma(p, z, 0x1.999999997fd9cp-3);
+    p = fma(p, z, 0x1.5555555555592p-2);
     const double s2 = 2.0 * sv;
     const double lnm = fma(s2 * z, p, s2);
     const double de = (double)e;
     return fma(de, 0x1.62e42fefa4000p-1, fma(de, -0x1.8432a1b0e2634p-43, lnm));
 }
 
-// sin and cos of 2 pi u: the angle is n pi 2^-21 with n = 2 b + 1; its quarter turns q = n >> 20
-// and the odd rest m = n mod 2^20 reduce it exactly to x = m' pi 2^-21 in (0, pi/4] (m' = m, or
-// 2^20 - m with sine and cosine exchanged); sin x and cos x by their Taylor series to x^17 and
-// x^18 (truncation below 1e-19).
+// sin and cos of 2 pi u: the angle is n pi 2^-21 with n = 2 b + 1; its quarter turn q = b >> 19 and
+// the odd rest m = n mod 2^20 reduce it exactly to x = m' pi 2^-21 in (0, pi/4], m' = m or, past
+// the eighth turn (bit 18 of b), 2^20 - m with sine and cosine exchanged; they are exchanged again in
+// the odd quarters, sin is negative in the last two and cos in the middle two.
 __host__ __device__ inline void u21_sincos_turn(uint32_t b, double &sn, double &cs)
 {
-    const uint32_t n = 2u * b + 1u, q = n >> 20, m = n & 0xFFFFFu;
-    const bool comp = m > 0x80000u;
-    const double x = (double)(comp ? 0x100000u - m : m) * 0x1.921fb54442d18p-20;   // pi 2^-21
+    const uint32_t past = (uint32_t)((int32_t)(b << 13) >> 31);   // all ones when bit 18 is set
+    const uint32_t m = (((2u * b + 1u) ^ past) & 0xFFFFFu) | 1u;
+    const double x = (double)m * 0x1.921fb54442d18p-20;   // pi 2^-21
     const double z = x * x;
-    double ps = 1.0 / 355687428096000.0;   // 1/17!
-    ps = fma(ps, z, -1.0 / 1307674368000.0);
-    ps = fma(ps, z, 1.0 / 6227020800.0);
-    ps = fma(ps, z, -1.0 / 39916800.0);
-    ps = fma(ps, z, 1.0 / 362880.0);
-    ps = fma(ps, z, -1.0 / 5040.0);
-    ps = fma(ps, z, 1.0 / 120.0);
-    ps = fma(ps, z, -1.0 / 6.0);
+    double ps = 0x1.5d92fa85c3980p-33;
+    ps = fma(ps, z, -0x1.ae5e660a2b2c3p-26);
+    ps = fma(ps, z, 0x1.71de357755567p-19);
+    ps = fma(ps, z, -0x1.a01a019c11080p-13);
+    ps = fma(ps, z, 0x1.111111110f876p-7);
+    ps = fma(ps, z, -0x1.5555555555549p-3);
     const double sx = fma(x * z, ps, x);
-    double pc = -1.0 / 6402373705728000.0;   // -1/18!
-    pc = fma(pc, z, 1.0 / 20922789888000.0);
-    pc = fma(pc, z, -1.0 / 87178291200.0);
-    pc = fma(pc, z, 1.0 / 479001600.0);
-    pc = fma(pc, z, -1.0 / 3628800.0);
-    pc = fma(pc, z, 1.0 / 40320.0);
-    pc = fma(pc, z, -1.0 / 720.0);
-    pc = fma(pc, z, 1.0 / 24.0);
+    double pc = -0x1.8fb15f588136cp-37;
+    pc = fma(pc, z, 0x1.1ee9f120bd1d2p-29);
+    pc = fma(pc, z, -0x1.27e4f81155b54p-22);
+    pc = fma(pc, z, 0x1.a01a019cbb6dcp-16);
+    pc = fma(pc, z, -0x1.6c16c16c151dbp-10);
+    pc = fma(pc, z, 0x1.555555555554cp-5);
     pc = fma(pc, z, -0.5);
     const double cx = fma(z, pc, 1.0);
-    const double s0 = comp ? cx : sx, c0 = comp ? sx : cx;   // of the rest m pi 2^-21
-    sn = q == 0 ? s0 : (q == 1 ? c0 : (q == 2 ? -s0 : -c0));
-    cs = q == 0 ? c0 : (q == 1 ? -s0 : (q == 2 ? -c0 : s0));
+    const bool swap = ((b + (1u << 18)) & (1u << 19)) != 0;   // bit 18 xor bit 19
+    const double s0 = swap ? cx : sx, c0 = swap ? sx : cx;
+    const unsigned long long ss = (unsigned long long)((b << 11) & 0x80000000u) << 32;
+    const unsigned long long sc = (unsigned long long)(((b + (1u << 19)) << 11) & 0x80000000u) << 32;
+    sn = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, s0) ^ ss);
+    cs = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, c0) ^ sc);
 }
 
 template <typename R> struct Gauss;
@@ -154,7 +216,7 @@ template <> struct Gauss<double> {
     static __device__ __forceinline__ void pair(uint32_t be, uint32_t bo, double &a, double &b)
     {
 #pragma clang fp contract(on)
-        const double r = sqrt(-2.0 * u21_ln(be));
+        const double r = sqrt64(-2.0 * u21_ln(be));
         double s, c;
         u21_sincos_turn(bo, s, c);
         a = r * c;
@@ -162,7 +224,9 @@ template <> struct Gauss<double> {
     }
 };
 
-// Box-Muller with the radius scaled: scale * (the pair above)
+// Box-Muller with the radius scaled.  noise_scale(v, sqrt(v)) is what the pairs take for normals of
+// variance v: the root in float; v itself in double, where it goes under the radius' root.
+template <typename R> __device__ __forceinline__ R noise_scale(R var, R root) { return sizeof(R) == 8 ? var : root; }
 template <typename R> __device__ __forceinline__ void gauss_pair_scaled(uint32_t be, uint32_t bo, R scale, R &a, R &b);
 template <> __device__ __forceinline__ void gauss_pair_scaled<float>(uint32_t be, uint32_t bo, float scale, float &a, float &b)
 {
@@ -176,14 +240,14 @@ template <> __device__ __forceinline__ void gauss_pair_scaled<float>(uint32_t be
 template <> __device__ __forceinline__ void gauss_pair_scaled<double>(uint32_t be, uint32_t bo, double scale, double &a, double &b)
 {
 #pragma clang fp contract(on)
-    const double r = sqrt(-2.0 * u21_ln(be)) * scale;
+    const double r = sqrt64(-2.0 * u21_ln(be) * scale);
     double s, c;
     u21_sincos_turn(bo, s, c);
     a = r * c;
     b = r * s;
 }
 
-// the six normals of (node, rep, t), each multiplied by `scale`
+// the six normals of (node, rep, t) of the variance that `scale` (noise_scale) stands for
 template <typename R>
 __device__ __forceinline__ void normals6s(uint32_t node, uint32_t rep, unsigned long long t, uint32_t k0,
                                           uint32_t k1, R scale, R nu[6])

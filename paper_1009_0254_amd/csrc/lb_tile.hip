@@ -17,10 +17,10 @@
 // in x).  Tiles of 128 or 256 columns were slower at every size.
 //
 // What bounds it: below ~2^17 nodes the chain of a launch (~2 us to the first collision, then 1.5 us
-// a step in FP32, 3.5 us in FP64: the collision's own dependent instructions); from ~2^19 nodes VALU
+// a step in FP32, 3 us in FP64: the collision's own dependent instructions); from ~2^19 nodes VALU
 // issue, the lost rows included (2048 x 400 in FP32: 25 us for 9.2 M wave instructions per two
-// steps).  Measured, us per step, k_step2's 16-row tiles before and these after: 64^2 FP64 41 / 4.2,
-// 128^2 FP32 24 / 2.6, 512^2 FP32 23.6 / 6.0, 2048 x 400 FP32 24.8 / 12.5, FP64 45 / 27.6,
+// steps).  Measured, us per step, k_step2's 16-row tiles before and these after: 64^2 FP64 41 / 3.6,
+// 128^2 FP32 24 / 2.6, 512^2 FP32 23.6 / 6.0, 2048 x 400 FP32 24.8 / 12.5, FP64 45 / 23.6,
 // 1500 x 1101 FP32 30.6 / 21.3.
 
 #include "lb_collide.h"
