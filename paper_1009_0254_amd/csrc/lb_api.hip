@@ -89,8 +89,9 @@ struct Layout {
     size_t sk_tw, sk_reps, spec, acc, sk_base;   // structure factor
     int sk_G, sk_nmax;
     long long sk_ptot;
-    size_t xi, cn_a, cn_tw;     // correlated noise
+    size_t xi, cn_tw;           // correlated noise
     long long cn_nodes, cn_max_n, cn_tw_elems;
+    int cn_planes;
     size_t total;
     long long nodes;      // sum of nx*ny
     long long max_n;      // largest replica
@@ -246,8 +247,10 @@ Layout make_layout(const lb_params *p, int32_t n_rep, int32_t precision, uint32_
         L.sk_base = o; o += align_up(sizeof(double) * 18 * (size_t)n_rep);
     }
     if (L.cn_nodes > 0) {
-        L.xi = o; o += align_up((size_t)4 * L.cn_nodes * elem_size(precision));   // planes of steps t, t + 1
-        L.cn_a = o; o += align_up(sizeof(double) * 2 * (size_t)L.cn_max_n);
+        // planes of steps t, t + 1; of four steps for one correlated replica in FP32 (the bytes that
+        // the fields' FP64 scratch plane, now in the population buffers, took)
+        L.cn_planes = precision != LB_FP64 && L.cn_nodes == L.cn_max_n ? 4 : 2;
+        L.xi = o; o += align_up((size_t)2 * L.cn_planes * L.cn_nodes * elem_size(precision));
         L.cn_tw = o; o += align_up(sizeof(double) * 2 * (size_t)L.cn_tw_elems);
     }
     L.total = o;
@@ -304,7 +307,7 @@ struct lb_handle {
     // correlated noise
     std::vector<int> cn_reps;
     void *xi = nullptr;
-    double *cn_a = nullptr, *cn_tw = nullptr;
+    double *cn_tw = nullptr;
 };
 
 namespace {
@@ -412,13 +415,25 @@ lb_status set_tiles(lb_handle *h, int bx, double rows)
     return LB_OK;
 }
 
-hipError_t step_once(lb_handle *h, int par, int toff, hipStream_t s)
+// the correlated noise of nsteps (1, 2 or 4) steps from time t + toff, in planes 0 .. nsteps - 1 of the
+// xi buffer, before the launch that takes buffer par into par ^ 1.  Its scratch is the replica's part of
+// buffer par ^ 1, which that launch overwrites: 2 nsteps nx ny of its 9 nx ny elements, and less than 256
+// bytes for the alignment (nx ny >= 16; >= 64 with four steps).
+hipError_t enqueue_noise(lb_handle *h, int par, int toff, int nsteps, hipStream_t s)
 {
     for (int r : h->cn_reps) {
-        hipError_t e = launch_correlated_noise(h->precision, h->reps_d, h->reps[r], r, h->cn_a, h->cn_tw,
-                                               h->xi, h->tdev, toff, s);
+        const uintptr_t part = (uintptr_t)h->fbuf[par ^ 1] + (size_t)h->reps[r].off * elem_size(h->precision);
+        hipError_t e = launch_correlated_noise(h->precision, h->reps_d, h->reps[r], r, (void *)align_up(part), h->cn_tw,
+                                               h->xi, 2 * h->L.cn_nodes, h->tdev, toff, nsteps, s);
         if (e != hipSuccess) return e;
     }
+    return hipSuccess;
+}
+
+hipError_t step_once(lb_handle *h, int par, int toff, hipStream_t s)
+{
+    hipError_t e = enqueue_noise(h, par, toff, 1, s);
+    if (e != hipSuccess) return e;
     StepLaunch a;
     a.xi = h->xi;
     a.fin = h->fbuf[par];
@@ -458,13 +473,8 @@ lb_status set_tiles2(lb_handle *h, int bx, double rows)
 hipError_t step_pair(lb_handle *h, int par, int toff, hipStream_t s)
 {
     const int64_t plane = 2 * h->L.cn_nodes;
-    for (int j = 0; j < 2; ++j)
-        for (int r : h->cn_reps) {
-            void *xi = (char *)h->xi + (size_t)j * plane * elem_size(h->precision);
-            hipError_t e = launch_correlated_noise(h->precision, h->reps_d, h->reps[r], r, h->cn_a, h->cn_tw, xi,
-                                                   h->tdev, toff + j, s);
-            if (e != hipSuccess) return e;
-        }
+    hipError_t e = enqueue_noise(h, par, toff, 2, s);
+    if (e != hipSuccess) return e;
     Step2Launch a;
     a.xi = h->cn_reps.empty() ? nullptr : h->xi;
     a.xi_plane = plane;
@@ -537,21 +547,14 @@ void node_tile_shape(const lb_handle *h, int *ns, int *ty)
         if (count(2, *ty) <= ncu) return;
 }
 
-// nt[which].ns steps from time t + toff, buffer par into buffer par ^ 1 (correlated noise first, a
-// plane a step)
-hipError_t step_tile(lb_handle *h, int which, int par, int toff, hipStream_t s)
+// nt[which].ns steps from time t + toff, buffer par into buffer par ^ 1, with the correlated noise in
+// planes xi0 .. of the xi buffer
+hipError_t step_tile(lb_handle *h, int which, int par, int toff, int xi0, hipStream_t s)
 {
     const lb_handle::NodeTiles &q = h->nt[which];
     const int64_t plane = 2 * h->L.cn_nodes;
-    for (int j = 0; j < q.ns; ++j)
-        for (int r : h->cn_reps) {
-            void *xi = (char *)h->xi + (size_t)j * plane * elem_size(h->precision);
-            hipError_t e = launch_correlated_noise(h->precision, h->reps_d, h->reps[r], r, h->cn_a, h->cn_tw, xi,
-                                                   h->tdev, toff + j, s);
-            if (e != hipSuccess) return e;
-        }
     TileLaunch a;
-    a.xi = h->cn_reps.empty() ? nullptr : h->xi;
+    a.xi = h->cn_reps.empty() ? nullptr : (const char *)h->xi + (size_t)xi0 * plane * elem_size(h->precision);
     a.xi_plane = plane;
     a.fin = h->fbuf[par];
     a.fout = h->fbuf[par ^ 1];
@@ -575,12 +578,23 @@ hipError_t enqueue_steps(lb_handle *h, long long n, int *par, int toff, hipStrea
 {
     long long k = 0;
     if (h->tns) {
+        // correlated noise: the fields of as many steps at once as there are planes (each of the two
+        // noise kernels is a chain of its own, ~3.5 us on a small lattice for one step or four)
+        const bool cn = !h->cn_reps.empty();
+        int have = 0, used = 0;   // steps whose fields are made, and taken
         while (k < n) {
-            const int which = n - k >= h->tns ? 0 : 1;
-            hipError_t e = step_tile(h, which, *par, toff + (int)k, s);
+            const int which = n - k >= h->tns ? 0 : 1, ns = h->nt[which].ns;
+            if (cn && used == have) {
+                have = n - k >= 4 && h->tns == 2 && h->L.cn_planes >= 4 && h->L.cn_nodes >= 64 ? 4 : ns;
+                used = 0;
+                hipError_t e = enqueue_noise(h, *par, toff + (int)k, have, s);
+                if (e != hipSuccess) return e;
+            }
+            hipError_t e = step_tile(h, which, *par, toff + (int)k, used, s);
             if (e != hipSuccess) return e;
             *par ^= 1;
-            k += h->nt[which].ns;
+            k += ns;
+            used += ns;
         }
         return hipSuccess;
     }
@@ -1034,7 +1048,6 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
 
     if (L.cn_nodes > 0) {
         h->xi = h->ws + L.xi;
-        h->cn_a = (double *)(h->ws + L.cn_a);
         h->cn_tw = (double *)(h->ws + L.cn_tw);
     }
     long long off = 0, node_off = 0, xi_off = 0, tw_off = 0;
@@ -1073,16 +1086,13 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
         return LB_EDEVICE;
     }
     if (e == hipSuccess && !h->cn_reps.empty()) {
-        int max_nx = 0, max_ny = 0;
         for (int r : h->cn_reps) {
             const RepDesc &d = h->reps[r];
-            max_nx = std::max(max_nx, d.nx);
-            max_ny = std::max(max_ny, d.ny);
             double *tw = h->cn_tw + 2 * d.tw_off;
             if (e == hipSuccess) e = launch_twiddles(tw, d.nx, h->stream);
             if (e == hipSuccess) e = launch_twiddles(tw + 2 * (d.nx / 2), d.ny, h->stream);
         }
-        if (e == hipSuccess) e = set_fft_lds_limit(max_nx, max_ny);
+        if (e == hipSuccess) e = set_fft_lds_limit();
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) {
             delete h;

@@ -51,6 +51,7 @@ __global__ void k_fill(double *p, long long n, double v)
 
 constexpr int CN_THREADS = 1024;
 constexpr int CN_COL_POINTS = 4096;   // points per drawing block when columns are short
+constexpr int CN_MIN_BLOCKS = 128;    // drawing blocks per step that short columns are spread over
 constexpr int CN_LDS_POINT_BYTES = 131072;   // largest transform batch of one block, in bytes (before its 1/16 pad)
 
 int cn_threads(int points) { return points >= 4096 ? 1024 : 256; }
@@ -69,6 +70,9 @@ struct CnGen {
     int blocks;
     int points;      // transform points held by a block
 };
+// Short columns share a block only as far as that leaves CN_MIN_BLOCKS blocks: a 128 x 128 lattice in
+// 4 blocks of 32 columns took 6.6 us a launch for one step's fields, in 64 blocks of one pair CNGEN_US us
+// for four steps'.
 CnGen cn_gen_shape(int nx, int ny, size_t elem)
 {
     CnGen g;
@@ -76,6 +80,7 @@ CnGen cn_gen_shape(int nx, int ny, size_t elem)
     if (g.paired) {
         const int want = ny >= CN_COL_POINTS / 2 ? 1 : CN_COL_POINTS / (2 * ny);
         g.per_block = want < nx / 2 ? want : nx / 2;
+        while (g.per_block > 1 && (nx / 2) / g.per_block < CN_MIN_BLOCKS) g.per_block /= 2;
         g.blocks = (nx / 2) / g.per_block;
         g.points = 2 * g.per_block * ny;
     } else {
@@ -209,6 +214,7 @@ __device__ __forceinline__ long long cn_a_at(int kx, int y, int nx, int lch)
 // precision R), stored to the intermediate plane.  PAIRED: `per` mirror pairs of columns
 // (slots 2i, 2i + 1 hold pair p0 + i), each pair's normals drawn once; else `per` adjacent
 // columns.
+// blockIdx.y: the step after tdev[0] + toff, whose plane of the scratch is the blockIdx.y-th.
 template <typename R, bool PAIRED>
 __global__ void __launch_bounds__(CN_THREADS) k_cn_gen(void *__restrict__ Av, const RepDesc *__restrict__ reps,
                                                        int rep_index, int per, int nblocks,
@@ -225,7 +231,7 @@ __global__ void __launch_bounds__(CN_THREADS) k_cn_gen(void *__restrict__ Av, co
     const long long lb = xcd_logical(nblocks);
     if (lb < 0) return;
     const int first = (int)lb * per;
-    const unsigned long long t = tdev[0] + (unsigned long long)toff;
+    const unsigned long long t = tdev[0] + (unsigned long long)toff + blockIdx.y;
     tw_cache_load(T, twy, ny);
     // 1/16-pad layout, filled in destination order: lane e writes slot e of the bit-reversed
     // column (its ky is bitrev(e)), radix-16 passes with the remainder last
@@ -270,7 +276,7 @@ __global__ void __launch_bounds__(CN_THREADS) k_cn_gen(void *__restrict__ Av, co
     }
     __syncthreads();
     cn_fft<R>(X, logny, cols, T, ny);
-    C *A = reinterpret_cast<C *>(Av);
+    C *A = reinterpret_cast<C *>(Av) + (long long)blockIdx.y * nx * ny;
     const int lch = cn_chunk_log(logny);
     for (int e = threadIdx.x; e < (cols << logny); e += blockDim.x) {
         const int sl = e >> logny, y = e & (ny - 1);
@@ -289,10 +295,11 @@ __global__ void __launch_bounds__(CN_THREADS) k_cn_gen(void *__restrict__ Av, co
 // rows (contiguous).  Consecutive blocks, which read the same cache lines, run at the same
 // time on one XCD.  Two rows per block when they fit: the gather is bound by the number of
 // requests (one per lane and kx), which the second row halves.
+// blockIdx.y: the step, its plane of the scratch and of the fields (xi_plane elements apart).
 template <typename S, int ROWS>
 __global__ void __launch_bounds__(CN_THREADS) k_cn_out(const void *__restrict__ Av, S *__restrict__ xi,
-                                                       const RepDesc *__restrict__ reps, int rep_index,
-                                                       const double2 *__restrict__ twx)
+                                                       long long xi_plane, const RepDesc *__restrict__ reps,
+                                                       int rep_index, const double2 *__restrict__ twx)
 {
     typedef typename V2<S>::type C;
     typedef typename std::conditional<sizeof(S) == 4, float4, double4>::type Q;
@@ -300,9 +307,9 @@ __global__ void __launch_bounds__(CN_THREADS) k_cn_out(const void *__restrict__ 
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ TwCacheT<S> T;
     C *X = reinterpret_cast<C *>(smem_raw);
-    const C *A = reinterpret_cast<const C *>(Av);
     const RepDesc &d = reps[rep_index];
     const int nx = d.nx, ny = d.ny, lognx = d.lognx;
+    const C *A = reinterpret_cast<const C *>(Av) + (long long)blockIdx.y * nx * ny;
     const long long lr = xcd_logical(ny / ROWS);
     if (lr < 0) return;
     const int y0 = (int)lr * ROWS;
@@ -334,69 +341,69 @@ __global__ void __launch_bounds__(CN_THREADS) k_cn_out(const void *__restrict__ 
     __syncthreads();
     cn_fft<S>(X, lognx, ROWS, T, nx);
     const S s = (S)rsqrt((double)nx * (double)ny);
-    C *out = reinterpret_cast<C *>(xi + 2 * d.xi_off) + (long long)y0 * nx;
+    C *out = reinterpret_cast<C *>(xi + blockIdx.y * xi_plane + 2 * d.xi_off) + (long long)y0 * nx;
     for (int e = threadIdx.x; e < ROWS * nx; e += blockDim.x) {
         const C v = X[lds_at(e, sh)];
         out[e] = mk2(v.x * s, v.y * s);
     }
 }
 
-template <typename R> static hipError_t set_cn_limits(int max_nx, int max_ny)
+// the largest transform batch of a block, padded
+template <typename R> static hipError_t set_cn_limits()
 {
     typedef typename V2<R>::type C;
-    const CnGen g = cn_gen_shape(max_nx, max_ny, sizeof(C));
-    const int gb = (int)(sizeof(C) * lds_padded16(g.points));
-    const int ob = (int)(sizeof(C) * lds_padded16((long long)cn_out_rows(max_nx, sizeof(C)) * max_nx));
-    hipError_t e = hipFuncSetAttribute((const void *)k_cn_gen<R, true>, hipFuncAttributeMaxDynamicSharedMemorySize, gb);
+    const int bytes = (int)(sizeof(C) * lds_padded16(CN_LDS_POINT_BYTES / sizeof(C)));
+    hipError_t e = hipFuncSetAttribute((const void *)k_cn_gen<R, true>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_cn_gen<R, false>, hipFuncAttributeMaxDynamicSharedMemorySize, gb);
+        e = hipFuncSetAttribute((const void *)k_cn_gen<R, false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_cn_out<R, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, ob);
+        e = hipFuncSetAttribute((const void *)k_cn_out<R, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_cn_out<R, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, ob);
+        e = hipFuncSetAttribute((const void *)k_cn_out<R, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     return e;
 }
 
-// the dynamic LDS of a block grows with nx and ny, so the largest sides bound every replica's
-hipError_t set_fft_lds_limit(int max_nx, int max_ny)
+hipError_t set_fft_lds_limit()
 {
-    hipError_t e = set_cn_limits<double>(max_nx, max_ny);
-    return e == hipSuccess ? set_cn_limits<float>(max_nx, max_ny) : e;
+    hipError_t e = set_cn_limits<double>();
+    return e == hipSuccess ? set_cn_limits<float>() : e;
 }
 
 template <typename R>
-static void launch_cn_t(const RepDesc *d_reps, const RepDesc &h, int rep_index, double *work, const double2 *twx,
-                        const double2 *twy, R *xi, const unsigned long long *tdev, int toff, hipStream_t s)
+static void launch_cn_t(const RepDesc *d_reps, const RepDesc &h, int rep_index, void *work, const double2 *twx,
+                        const double2 *twy, R *xi, long long xi_plane, const unsigned long long *tdev, int toff,
+                        int nsteps, hipStream_t s)
 {
     typedef typename V2<R>::type C;
     const CnGen g = cn_gen_shape(h.nx, h.ny, sizeof(C));
     const size_t gb = sizeof(C) * lds_padded16(g.points);
+    const dim3 gen(xcd_grid(g.blocks), nsteps);
     if (g.paired)
-        hipLaunchKernelGGL((k_cn_gen<R, true>), dim3(xcd_grid(g.blocks)), dim3(cn_threads(g.points)), gb,
-                           s, (void *)work, d_reps, rep_index, g.per_block, g.blocks, twy, tdev, toff);
+        hipLaunchKernelGGL((k_cn_gen<R, true>), gen, dim3(cn_threads(g.points)), gb, s, work, d_reps, rep_index,
+                           g.per_block, g.blocks, twy, tdev, toff);
     else
-        hipLaunchKernelGGL((k_cn_gen<R, false>), dim3(xcd_grid(g.blocks)), dim3(cn_threads(g.points)),
-                           gb, s, (void *)work, d_reps, rep_index, g.per_block, g.blocks, twy, tdev, toff);
+        hipLaunchKernelGGL((k_cn_gen<R, false>), gen, dim3(cn_threads(g.points)), gb, s, work, d_reps, rep_index,
+                           g.per_block, g.blocks, twy, tdev, toff);
     const int rows = cn_out_rows(h.nx, sizeof(C));
     const size_t ob = sizeof(C) * lds_padded16((long long)rows * h.nx);
     if (rows == 2)
-        hipLaunchKernelGGL((k_cn_out<R, 2>), dim3(xcd_grid(h.ny / 2)), dim3(cn_threads(2 * h.nx)), ob, s,
-                           (const void *)work, xi, d_reps, rep_index, twx);
+        hipLaunchKernelGGL((k_cn_out<R, 2>), dim3(xcd_grid(h.ny / 2), nsteps), dim3(cn_threads(2 * h.nx)), ob, s,
+                           (const void *)work, xi, xi_plane, d_reps, rep_index, twx);
     else
-        hipLaunchKernelGGL((k_cn_out<R, 1>), dim3(xcd_grid(h.ny)), dim3(cn_threads(h.nx)), ob, s, (const void *)work, xi,
-                           d_reps, rep_index, twx);
+        hipLaunchKernelGGL((k_cn_out<R, 1>), dim3(xcd_grid(h.ny), nsteps), dim3(cn_threads(h.nx)), ob, s,
+                           (const void *)work, xi, xi_plane, d_reps, rep_index, twx);
 }
 
-hipError_t launch_correlated_noise(int precision, const RepDesc *d_reps, const RepDesc &h_rep, int rep_index,
-                                   double *work, const double *tw_base, void *xi_base,
-                                   const unsigned long long *tdev, int toff, hipStream_t s)
+hipError_t launch_correlated_noise(int precision, const RepDesc *d_reps, const RepDesc &h_rep, int rep_index, void *work,
+                                   const double *tw_base, void *xi_base, long long xi_plane,
+                                   const unsigned long long *tdev, int toff, int nsteps, hipStream_t s)
 {
     const double2 *twx = (const double2 *)tw_base + h_rep.tw_off;
     const double2 *twy = twx + h_rep.nx / 2;
     if (precision == 0)
-        launch_cn_t<double>(d_reps, h_rep, rep_index, work, twx, twy, (double *)xi_base, tdev, toff, s);
+        launch_cn_t<double>(d_reps, h_rep, rep_index, work, twx, twy, (double *)xi_base, xi_plane, tdev, toff, nsteps, s);
     else
-        launch_cn_t<float>(d_reps, h_rep, rep_index, work, twx, twy, (float *)xi_base, tdev, toff, s);
+        launch_cn_t<float>(d_reps, h_rep, rep_index, work, twx, twy, (float *)xi_base, xi_plane, tdev, toff, nsteps, s);
     return hipGetLastError();
 }
 

@@ -185,13 +185,14 @@ hipError_t launch_philox(uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uin
 
 // twiddles exp(-2 pi i j / n), j < n/2, as (re, im) pairs (lb_fft.hip)
 hipError_t launch_twiddles(double *tw, int n, hipStream_t s);
-// correlated noise of one replica for step time tdev[0] + toff: fills its xi plane, using
-// `work` (nx ny complex doubles) as scratch
+// correlated noise of one replica for the step times tdev[0] + toff .. + nsteps - 1: fills its part
+// of nsteps xi planes (xi_plane elements of the storage type apart), using `work` (nsteps nx ny
+// complex elements of the storage type, 32-byte aligned) as scratch
 hipError_t launch_correlated_noise(int precision, const RepDesc *d_reps, const RepDesc &h_rep, int rep_index,
-                                   double *work, const double *tw_base, void *xi_base,
-                                   const unsigned long long *tdev, int toff, hipStream_t s);
-// LDS limits of the correlated-noise kernels for replicas up to max_nx x max_ny
-hipError_t set_fft_lds_limit(int max_nx, int max_ny);
+                                   void *work, const double *tw_base, void *xi_base, long long xi_plane,
+                                   const unsigned long long *tdev, int toff, int nsteps, hipStream_t s);
+// LDS limits of the correlated-noise kernels
+hipError_t set_fft_lds_limit();
 
 // structure factor (lb_sk.hip).  Replicas are sampled together: every pass covers a range
 // [r0, r1) of replicas with one launch per kernel, whatever their sizes.

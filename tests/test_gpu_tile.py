@@ -37,6 +37,8 @@ CASES = [
                     W.single_phase(100, 36, kT=1e-5, seed=32, replica=1),
                     dict(W.correlated_sec5a(256, 16, kT=1e-6, seed=33), replica=2)]),
 ]
+CASES += [("correlated-" + f"{nx}x{ny}", [W.correlated_sec5a(nx, ny, kT=1e-6, seed=34)])   # four steps' fields at once
+          for nx, ny in ((4, 4), (8, 8), (128, 32))]                              # (from 64 nodes on, FP32)
 TILES = ["1,4", "1,16", "2,5", "2,8", "2,16", "4,13", "4,16", None]   # None: the handle's own choice
 
 
@@ -60,7 +62,7 @@ def test_node_tiles_bitwise(monkeypatch, label, cfgs, precision):
 
     _, ref = run({"LBF_TILE": "256,16", "LBF_STEPS_PER_LAUNCH": "1"})
     for tile in TILES:
-        if tile and tile[0] == "4" and (precision == 0 or label == "correlated"):
+        if tile and tile[0] == "4" and (precision == 0 or label.startswith("correlated")):
             continue   # four steps: FP32 without correlated noise only
         print("[gpu-tile]", label, "precision", precision, "tile", tile, file=sys.stderr, flush=True)
         steps, got = run({"LBF_NODE_TILE": tile} if tile else {})
