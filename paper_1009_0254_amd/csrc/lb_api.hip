@@ -178,6 +178,27 @@ lb_status validate(const lb_params *p, int32_t n_rep, int32_t precision)
 // rows per row workgroup: narrow rows are grouped to 512 complex points
 int sk_rows_per_block(int nx, int ny) { return std::max(1, std::min(ny, 1024 / nx)); }
 
+// column blocks of a replica: nh = nx/2 + 1 columns, cpb a block; with fold the last block takes one more
+// instead of leaving column nx/2 a block of its own
+long long sk_col_blocks(int nh, int cpb, int split, int fold)
+{
+    return (long long)split * (fold ? std::max(1, (nh - 1) / cpb) : (nh + cpb - 1) / cpb);
+}
+
+// By how much the rows or columns per block are cut when the whole handle gives fewer blocks than
+// SK_MIN_*_BLOCKS (times nine modes for the columns): a small lattice's sample is a chain of its blocks'
+// passes, not a throughput (128^2, one sample: 26 us in 16 row and 2 x 9 column blocks, 13 us cut).
+constexpr int SK_MIN_ROW_BLOCKS = 256, SK_MIN_COL_BLOCKS = 128;
+template <typename F> int sk_divisor(int n_rep, int min_blocks, F blocks_of)
+{
+    for (int div = 1;; div *= 2) {
+        long long n = 0;
+        bool more = false;
+        for (int r = 0; r < n_rep; ++r) n += blocks_of(r, div, &more);
+        if (n >= min_blocks || !more) return div;
+    }
+}
+
 // the S(k) feature needs power-of-two sides in [4, SK_MAX] on every replica
 lb_status validate_features(const lb_params *p, int32_t n_rep, uint32_t features)
 {
@@ -645,10 +666,11 @@ SkLaunch sk_launch(const lb_handle *h, int r0, int r1, int par)
     a.col_base = q0.col0;
     a.rows = (r1 < h->n_rep ? h->sk[r1].row0 : h->sk_rows) - q0.row0;
     a.cols = (r1 < h->n_rep ? h->sk[r1].col0 : h->sk_cols) - q0.col0;
-    a.lds_rows = a.lds_cols = 0;
+    a.lds_rows = a.lds_cols = a.col_line = 0;
     for (int r = r0; r < r1; ++r) {
         a.lds_rows = std::max(a.lds_rows, h->sk[r].rpb * h->sk[r].nx);
-        a.lds_cols = std::max(a.lds_cols, h->sk[r].cpb * (h->sk[r].ny / h->sk[r].split));
+        a.col_line = std::max(a.col_line, h->sk[r].ny / h->sk[r].split);
+        a.lds_cols = std::max(a.lds_cols, (h->sk[r].cpb + h->sk[r].fold) * (h->sk[r].ny / h->sk[r].split));
     }
     a.G = h->L.sk_G;
     a.Ptot = h->L.sk_ptot;
@@ -1115,6 +1137,16 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
         h->sk_base = (double *)(h->ws + L.sk_base);
         long long rows = 0, cols = 0, soff = 0;
         int max_col = 0, max_row = 0;
+        const int row_div = sk_divisor(n_rep, SK_MIN_ROW_BLOCKS, [&](int r, int div, bool *more) -> long long {
+            const int rpb = std::max(1, sk_rows_per_block(p[r].nx, p[r].ny) / div);
+            *more = *more || rpb > 1;
+            return (p[r].ny + rpb - 1) / rpb;
+        });
+        const int col_div = sk_divisor(n_rep, SK_MIN_COL_BLOCKS, [&](int r, int div, bool *more) {
+            const int cpb = std::max(1, sk_cols_per_block(precision, p[r].nx, p[r].ny) / div), split = sk_split(precision, p[r].ny);
+            *more = *more || cpb > 1;
+            return sk_col_blocks(p[r].nx / 2 + 1, cpb, split, split == 1 && cpb > 1);
+        });
         for (int r = 0; r < n_rep; ++r) {
             SkRep q{};
             q.nx = p[r].nx;
@@ -1122,8 +1154,9 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
             q.lognx = ilog2(q.nx);
             q.logny = ilog2(q.ny);
             q.split = sk_split(precision, q.ny);
-            q.cpb = sk_cols_per_block(precision, q.nx, q.ny);
-            q.rpb = sk_rows_per_block(q.nx, q.ny);
+            q.cpb = std::max(1, sk_cols_per_block(precision, q.nx, q.ny) / col_div);
+            q.fold = q.split == 1 && q.cpb > 1 ? 1 : 0;
+            q.rpb = std::max(1, sk_rows_per_block(q.nx, q.ny) / row_div);
             q.logrpb = ilog2(q.rpb);
             const int nh = q.nx / 2 + 1;
             q.row0 = rows;
@@ -1132,9 +1165,9 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
             q.acc_off = (int64_t)h->acc_off[r];
             rows += (q.ny + q.rpb - 1) / q.rpb;
             max_row = std::max(max_row, q.rpb * q.nx);
-            cols += (long long)q.split * ((nh + q.cpb - 1) / q.cpb);
+            cols += sk_col_blocks(nh, q.cpb, q.split, q.fold);
             soff += (long long)q.ny * sk_nh_padded(q.nx);
-            max_col = std::max(max_col, q.cpb * (q.ny / q.split));
+            max_col = std::max(max_col, (q.cpb + q.fold) * (q.ny / q.split));
             h->sk.push_back(q);
         }
         h->sk_rows = rows;

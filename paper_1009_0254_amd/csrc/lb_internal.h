@@ -202,6 +202,7 @@ struct SkRep {
     int32_t nx, ny, lognx, logny;
     int32_t split;      // column blocks per kx: 1, or 2 (one per output parity) when a column does not fit
     int32_t cpb;        // adjacent kx columns per column block (1 when split)
+    int32_t fold;       // 1: the last column block takes column nx/2 too, as its (cpb + 1)-th
     int32_t rpb;        // rows per row block (a power of two)
     int32_t logrpb;     // log2(rpb)
     int64_t row0;       // first row block of this replica (prefix of ceil(ny / rpb))
@@ -218,7 +219,8 @@ struct SkLaunch {
     int64_t row_base, rows;   // row blocks of the range
     int64_t col_base, cols;
     int32_t lds_rows;         // most row points per block in the range (rpb * nx)
-    int32_t lds_cols;         // most column points per block in the range (cpb * ny, or ny/2 if split)
+    int32_t lds_cols;         // most column points per block in the range ((cpb + fold) * ny, or ny/2 if split)
+    int32_t col_line;         // longest column transform in the range (ny / split)
     int32_t G;                // modes per transform group of the row kernel
     int64_t Ptot;             // complex elements per mode slot (sum of ny * sk_nh_padded(nx) over all replicas)
     void *spec;               // nine mode slots of row spectra (float2 for FP32 storage, else double2)

@@ -41,9 +41,20 @@ namespace lbf {
 namespace {
 
 constexpr int SK_THREADS = 1024;   // upper bound; launches use fewer for short lines
+constexpr int SK_OWNREF_ROWS = 512;   // row blocks up to which each forms its reference itself
 
-// lines of 4096 points or more get 1024 lanes; shorter ones 256
-int sk_threads(int line) { return line >= 4096 ? 1024 : 256; }
+// Lanes of a row block (of `line` nodes) and of a column block (`points` in columns of `line`): a lane
+// keeps 8 points of a pass (4 in the FP64 columns) in registers, and more lanes than that asks for, or a
+// block so large that a CU holds only one, leave nothing to run beside its barriers.  us per sample:
+// 2048^2 FP32 rows 256 lanes 254, 512 231, 1024 268; FP64 484, 455, 450 with nine modes at a time, 437,
+// 415, 494 with four; 4096^2 FP32 with four modes 512 1079, with eight 1024 1189.  Columns: 1024^2 256
+// lanes 66, 512 62, 1024 76; ensemble of 336 replicas 606, 599, 632; 4096^2 (whole columns) 1481, 1279,
+// 1188.
+template <typename Tt> int sk_row_threads(int line)
+{
+    return line >= (sizeof(Tt) == 8 ? 4096 : 8192) ? 1024 : line >= 2048 ? 512 : 256;
+}
+int sk_col_threads(int line, int points) { return line >= 4096 ? 1024 : points > 1024 ? 512 : 256; }
 
 template <int F> __device__ __forceinline__ long long sk_key(const SkRep &q)
 {
@@ -176,18 +187,12 @@ constexpr int SK_REF_THREADS = 256;
 // is ~ sigma / sqrt(nx), so that neither the row sums (kx = 0) nor the totals carry an offset
 // that FP32 would have to resolve against the fluctuations.  base[18 r + a] = m_a(vref + shift)
 // in FP64, the constant the column pass restores at k = 0.
-template <typename S, typename Tt>
-__global__ void __launch_bounds__(SK_REF_THREADS)
-    k_sk_ref(const S *__restrict__ f, const RepDesc *__restrict__ reps, const SkRep *__restrict__ sk, int r0,
-             double *__restrict__ base)
+// Run by SK_REF_THREADS lanes; `out` is given to lane 0 only.
+template <typename S, typename Tt, typename F>
+__device__ __forceinline__ void sk_ref(const S *__restrict__ P, const SkRep &q, double (*part)[9], F out)
 {
-    __shared__ double part[SK_REF_THREADS / 64][9];
-    const int r = r0 + (int)blockIdx.x;
-    const SkRep &q = sk[r];
-    const RepDesc &d = reps[r];
-    const S *P = f + d.off;
     double s[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int x = threadIdx.x; x < q.nx; x += blockDim.x) {
+    for (int x = threadIdx.x; x < q.nx; x += SK_REF_THREADS) {
         S v[9];
         load_pull(P, q.nx, q.ny, x, 0, v);
 #pragma unroll
@@ -199,18 +204,33 @@ __global__ void __launch_bounds__(SK_REF_THREADS)
     if ((threadIdx.x & 63) == 0)
         for (int i = 0; i < 9; ++i) part[threadIdx.x >> 6][i] = s[i];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double g[9], m[9];
-        for (int i = 0; i < 9; ++i) {
-            double t = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += part[w][i];
-            const double vr = (double)(Tt)(t / q.nx);
-            base[18 * r + 9 + i] = vr;
-            g[i] = vr + d.shift[i];
-        }
-        moments9(g, m);
-        for (int a = 0; a < 9; ++a) base[18 * r + a] = m[a];
+    if (threadIdx.x < 9) {
+        double t = 0;
+        for (int w = 0; w < SK_REF_THREADS / 64; ++w) t += part[w][threadIdx.x];
+        out((int)threadIdx.x, (double)(Tt)(t / q.nx));
     }
+}
+
+// m_a(vref + shift) of replica r into base[18 r ..] (one lane)
+__device__ __forceinline__ void sk_ref_moments(const double *__restrict__ vr, const RepDesc &d, double *__restrict__ b)
+{
+    double g[9], m[9];
+    for (int i = 0; i < 9; ++i) g[i] = vr[i] + d.shift[i];
+    moments9(g, m);
+    for (int a = 0; a < 9; ++a) b[a] = m[a];
+}
+
+template <typename S, typename Tt>
+__global__ void __launch_bounds__(SK_REF_THREADS)
+    k_sk_ref(const S *__restrict__ f, const RepDesc *__restrict__ reps, const SkRep *__restrict__ sk, int r0,
+             double *__restrict__ base)
+{
+    __shared__ double part[SK_REF_THREADS / 64][9], vr[9];
+    const int r = r0 + (int)blockIdx.x;
+    const RepDesc &d = reps[r];
+    sk_ref<S, Tt>(f + d.off, sk[r], part, [&](int i, double v) { vr[i] = base[18 * r + 9 + i] = v; });
+    __syncthreads();
+    if (threadIdx.x == 0) sk_ref_moments(vr, d, base + 18 * r);
 }
 
 // Transforms run in Tt (float for FP32 storage, double for FP64) on m_a(r) - m_a(vref) (the
@@ -219,18 +239,21 @@ __global__ void __launch_bounds__(SK_REF_THREADS)
 // SK_CACHE_PAIRS) are pulled once and their nine moments kept in registers for all mode
 // groups, which are GC modes each and fixed at compile time (so that a placed group's
 // registers are free for the transforms); otherwise each group of G modes pulls the row
-// again (the repeats hit L2 or the MALL).
-template <typename S, typename Tt, int RMAX, bool CACHE, int GC>
+// again (the repeats hit L2 or the MALL).  OWNREF: every block forms its replica's reference itself
+// (blocks of SK_REF_THREADS lanes; the same sums in the same order) instead of reading k_sk_ref's,
+// and the replica's first block stores it for the column pass.
+template <typename S, typename Tt, int RMAX, bool CACHE, int GC, bool OWNREF = false>
 __global__ void __launch_bounds__(SK_THREADS)
     k_sk_rows(const S *__restrict__ f, const RepDesc *__restrict__ reps, const SkRep *__restrict__ sk, int r0, int r1,
               long long row_base, long long nrows, int a_first, int a_count, int G, long long Ptot,
-              typename V2<Tt>::type *__restrict__ spec, const double *__restrict__ base,
+              typename V2<Tt>::type *__restrict__ spec, double *__restrict__ base,
               const double2 *__restrict__ tw, int nmax)
 {
     typedef typename V2<Tt>::type C;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ TwCacheT<Tt> T;
     __shared__ Tt vref[9];
+    __shared__ double part[OWNREF ? SK_REF_THREADS / 64 : 1][9], vr[9];
     C *X = reinterpret_cast<C *>(smem_raw);
     const long long lr = xcd_logical(nrows);
     if (lr < 0) return;
@@ -246,8 +269,17 @@ __global__ void __launch_bounds__(SK_THREADS)
     const int pairs = R * M;
     const S *P = f + d.off;
     const int wstride = nmax / nx, sh = lds_pad_shift(logM);
-    if (threadIdx.x < 9) vref[threadIdx.x] = (Tt)base[18 * r + 9 + threadIdx.x];
+    if constexpr (OWNREF) {
+        sk_ref<S, Tt>(P, q, part, [&](int i, double v) {
+            vr[i] = v;
+            vref[i] = (Tt)v;
+        });
+        if (y0 == 0 && threadIdx.x < 9) base[18 * r + 9 + threadIdx.x] = vr[threadIdx.x];
+    } else {
+        if (threadIdx.x < 9) vref[threadIdx.x] = (Tt)base[18 * r + 9 + threadIdx.x];
+    }
     __syncthreads();   // vref (the reference)
+    if (OWNREF && y0 == 0 && threadIdx.x == 0) sk_ref_moments(vr, d, base + 18 * r);
     // (the cached variant pulls once; pulling in the permuted order every group costs more than
     // the fill's bank conflicts)
     const bool whole64 = CACHE && (pairs & 63) == 0;
@@ -322,14 +354,13 @@ __global__ void __launch_bounds__(SK_THREADS)
     };
     if constexpr (CACHE) {
         // the nine modes (a_first = 0, a_count = 9) in groups of GC
-        static_assert(GC == 4 || GC == 8, "cached rows run 4 + 4 + 1 or 8 + 1 modes");
+        static_assert(GC == 4, "cached rows run 4 + 4 + 1 modes");
         (void)a_first;
         (void)a_count;
         (void)G;
         run_group(std::integral_constant<int, 0>{}, std::integral_constant<int, GC>{}, 0, 0);
-        run_group(std::integral_constant<int, GC>{}, std::integral_constant<int, 9 - GC < GC ? 9 - GC : GC>{}, 0, 0);
-        if constexpr (2 * GC < 9)
-            run_group(std::integral_constant<int, 2 * GC>{}, std::integral_constant<int, 9 - 2 * GC>{}, 0, 0);
+        run_group(std::integral_constant<int, GC>{}, std::integral_constant<int, GC>{}, 0, 0);
+        run_group(std::integral_constant<int, 2 * GC>{}, std::integral_constant<int, 9 - 2 * GC>{}, 0, 0);
     } else {
         for (int a0 = a_first; a0 < a_first + a_count; a0 += G)
             run_group(std::integral_constant<int, -1>{}, std::integral_constant<int, -1>{}, a0,
@@ -338,7 +369,8 @@ __global__ void __launch_bounds__(SK_THREADS)
 }
 
 // column transforms of every replica in the range, reading the row spectra in place;
-// mode a = a_first + blockIdx.y.  A block takes cpb adjacent kx (reads coalesced along kx)
+// mode a = a_first + blockIdx.y.  A block takes cpb adjacent kx (reads coalesced along kx; the last
+// block of a replica cpb + fold)
 // or, for split lines, one kx and one output parity.  |X|^2 is formed in FP64, with the
 // k = 0 coefficient restored to X(0) + n m_a(vref + shift) (the row pass transformed moments
 // relative to the reference of k_sk_ref).  SNAP writes |X|^2 / n to plane ([nh][ny], one replica),
@@ -364,7 +396,7 @@ __global__ void __launch_bounds__(SK_THREADS)
     const int local = (int)(gc - q.col0);
     const int grp = local / split, par = local - grp * split;
     const int kx0 = grp * q.cpb;
-    const int C_ = min(q.cpb, nh - kx0);         // columns of this block
+    const int C_ = nh - kx0 <= q.cpb + q.fold ? nh - kx0 : q.cpb;   // columns of this block
     const int a = a_first + blockIdx.y;
     const C *S0 = spec + a * Ptot + q.soff;    // (y, kx) at S0[sk_at(y, kx, ny)]
     const double inv_n = 1.0 / ((double)q.nx * (double)ny);
@@ -378,8 +410,22 @@ __global__ void __launch_bounds__(SK_THREADS)
     const int sh = P16 ? LDS_PAD16 : lds_pad_shift(logL);
     if (split == 1) {
         if (P16) {
+            // four adjacent kx of a row by adjacent lanes: a wave's reads touch 16 cache lines instead of 64
+            const int n4 = q.cpb >= 4 ? q.cpb : 0;
+            for (int e0 = threadIdx.x; e0 < n4 << logL; e0 += 4 * blockDim.x) {
+                C v[4];
+                for (int u = 0; u < 4; ++u) {
+                    const int e = min(e0 + u * (int)blockDim.x, (n4 << logL) - 1);
+                    v[u] = S0[sk_at32((e >> 2) & (L - 1), kx0 + (e >> (2 + logL)) * 4 + (e & 3), ny)];
+                }
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + u * (int)blockDim.x, y = (e >> 2) & (L - 1);
+                    const int c = (e >> (2 + logL)) * 4 + (e & 3);
+                    if (e < n4 << logL) X[lds_at((c << logL) + (int)bitrev((unsigned)y, logL), sh)] = v[u];
+                }
+            }
             const int tot = C_ << logL;
-            for (int e0 = threadIdx.x; e0 < tot; e0 += 4 * blockDim.x) {
+            for (int e0 = (n4 << logL) + (int)threadIdx.x; e0 < tot; e0 += 4 * blockDim.x) {
                 C v[4];
                 for (int u = 0; u < 4; ++u) {
                     const int e = min(e0 + u * (int)blockDim.x, tot - 1);
@@ -522,35 +568,41 @@ __global__ void k_sk_read(const double *__restrict__ acc, double *__restrict__ o
 template <typename Tt> constexpr int SK_ROW_RADIX = 3;
 template <typename Tt> constexpr int SK_COL_RADIX = sizeof(Tt) == 4 ? 3 : 2;
 
-template <typename S, typename Tt, int RMAX, bool CACHE, int GC = 0>
+template <typename S, typename Tt, int RMAX, bool CACHE, int GC = 0, bool OWNREF = false>
 void rows_kernel(const SkLaunch &a, int a_first, int a_count, int G, int threads, hipStream_t s)
 {
     const size_t lds = (size_t)sk_elem(sizeof(Tt) == 8 ? 0 : 1) * lds_padded((long long)G * (a.lds_rows / 2));
-    hipLaunchKernelGGL((k_sk_rows<S, Tt, RMAX, CACHE, GC>), dim3(xcd_grid(a.rows)), dim3(threads), lds, s, (const S *)a.f,
+    hipLaunchKernelGGL((k_sk_rows<S, Tt, RMAX, CACHE, GC, OWNREF>), dim3(xcd_grid(a.rows)), dim3(threads), lds, s, (const S *)a.f,
                        a.reps, a.sk, a.r0, a.r1, (long long)a.row_base, (long long)a.rows, a_first, a_count, G,
                        (long long)a.Ptot, (typename V2<Tt>::type *)a.spec, a.base, (const double2 *)a.tw, a.nmax);
 }
 
 hipError_t launch_rows(int precision, const SkLaunch &a, int a_first, int a_count, hipStream_t s)
 {
+    const int G = a_count < a.G ? a_count : a.G;
+    const int threads = precision == 0 ? sk_row_threads<double>(a.lds_rows) : sk_row_threads<float>(a.lds_rows);
+    // a launch that does not fill the chip: one kernel fewer, a chain of ~5 us, for reading row 0 in every block
+    if (a.rows <= SK_OWNREF_ROWS && threads == SK_REF_THREADS) {
+        if (precision == 0)
+            rows_kernel<double, double, SK_ROW_RADIX<double>, false, 0, true>(a, a_first, a_count, G, threads, s);
+        else
+            rows_kernel<float, float, SK_ROW_RADIX<float>, false, 0, true>(a, a_first, a_count, G, threads, s);
+        return hipGetLastError();
+    }
     if (precision == 0)
         hipLaunchKernelGGL((k_sk_ref<double, double>), dim3((unsigned)(a.r1 - a.r0)), dim3(SK_REF_THREADS), 0, s,
                            (const double *)a.f, a.reps, a.sk, a.r0, a.base);
     else
         hipLaunchKernelGGL((k_sk_ref<float, float>), dim3((unsigned)(a.r1 - a.r0)), dim3(SK_REF_THREADS), 0, s,
                            (const float *)a.f, a.reps, a.sk, a.r0, a.base);
-    const int G = a_count < a.G ? a_count : a.G;
-    const int threads = sk_threads(a.lds_rows);
     // FP32: with at most SK_CACHE_PAIRS node pairs per lane the nine moments stay in
     // registers across the mode groups (FP64 would spill)
-    const bool cache = precision != 0 && a_first == 0 && a_count == 9 && (G == 4 || G == 8) &&
+    const bool cache = precision != 0 && a_first == 0 && a_count == 9 && G == 4 &&
                        a.lds_rows / 2 <= SK_CACHE_PAIRS * threads;
     if (precision == 0)
         rows_kernel<double, double, SK_ROW_RADIX<double>, false>(a, a_first, a_count, G, threads, s);
-    else if (cache && G == 4)
-        rows_kernel<float, float, SK_ROW_RADIX<float>, true, 4>(a, a_first, a_count, G, threads, s);
     else if (cache)
-        rows_kernel<float, float, SK_ROW_RADIX<float>, true, 8>(a, a_first, a_count, G, threads, s);
+        rows_kernel<float, float, SK_ROW_RADIX<float>, true, 4>(a, a_first, a_count, G, threads, s);
     else
         rows_kernel<float, float, SK_ROW_RADIX<float>, false>(a, a_first, a_count, G, threads, s);
     return hipGetLastError();
@@ -566,7 +618,7 @@ template <typename Tt, bool SNAP>
 void cols_kernel(int precision, const SkLaunch &a, unsigned modes, double *plane, hipStream_t s)
 {
     hipLaunchKernelGGL((k_sk_cols<Tt, SNAP, SK_COL_RADIX<Tt>>), dim3(xcd_grid(a.cols), modes),
-                       dim3(sk_threads(a.lds_cols)), sk_col_lds_bytes(precision, a.lds_cols), s,
+                       dim3(sk_col_threads(a.col_line, a.lds_cols)), sk_col_lds_bytes(precision, a.lds_cols), s,
                        (const typename V2<Tt>::type *)a.spec, a.sk, a.r0, a.r1, (long long)a.col_base,
                        (long long)a.cols, (long long)a.Ptot, 0, SNAP ? nullptr : a.acc, plane, (const double *)a.base,
                        (const double2 *)a.tw, a.nmax);
@@ -580,9 +632,9 @@ template <typename K> hipError_t lds_limit(K kernel, size_t bytes)
 template <typename S, typename Tt> hipError_t lds_limits_of(size_t rows, size_t cols)
 {
     hipError_t e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, false, 0>, rows);
-    if constexpr (sizeof(Tt) == 4) {   // the register-cached row variants exist for FP32 only
+    if (e == hipSuccess) e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, false, 0, true>, rows);
+    if constexpr (sizeof(Tt) == 4) {   // the register-cached row variant exists for FP32 only
         if (e == hipSuccess) e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, true, 4>, rows);
-        if (e == hipSuccess) e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, true, 8>, rows);
     }
     if (e == hipSuccess) e = lds_limit(k_sk_cols<Tt, false, SK_COL_RADIX<Tt>>, cols);
     if (e == hipSuccess) e = lds_limit(k_sk_cols<Tt, true, SK_COL_RADIX<Tt>>, cols);
@@ -593,22 +645,26 @@ template <typename S, typename Tt> hipError_t lds_limits_of(size_t rows, size_t 
 
 int sk_elem(int precision) { return precision == 0 ? (int)sizeof(double2) : (int)sizeof(float2); }
 
-// LDS budgets: the row kernel holds G half-length transforms of its widest rows in at most
-// 128 KiB; a column block holds at most 64 KiB (two blocks per CU)
-constexpr int ROW_BUDGET = 131072, COL_BUDGET = 65536;
+// LDS budgets: the row kernel holds G half-length transforms of its widest rows, in at most 72 KiB (two
+// blocks per CU) or, for lines of 4096 points, whose fewer modes would pull the row too often, 128 KiB;
+// a column block holds whole columns in 32 KiB, 16 KiB from 1024 points on (or one column, up to 64 KiB):
+// smaller blocks overlap each other's barriers and gathers (us per sample, blocks of 64 / 32 / 16 KiB: 2048^2
+// 300 / 278 / 254, 1024^2 68 / 63 / 61, ensemble of 336 replicas 650 / 632 / 651).
+constexpr int ROW_BUDGET = 73728, ROW_BUDGET_LONG = 131072, COL_BUDGET = 65536;
 
 int sk_modes_per_pass(int precision, int max_nx)
 {
     const int per_mode = sk_elem(precision) * (std::max(max_nx, 1024) / 2);
-    return std::max(1, std::min(9, ROW_BUDGET / per_mode));
+    const int budget = max_nx >= (precision == 0 ? 4096 : 8192) ? ROW_BUDGET_LONG : ROW_BUDGET;
+    return std::max(1, std::min(9, budget / per_mode));
 }
 
 int sk_split(int precision, int ny) { return (long long)ny * sk_elem(precision) > COL_BUDGET ? 2 : 1; }
 
 int sk_cols_per_block(int precision, int nx, int ny)
 {
-    const int pts = COL_BUDGET / sk_elem(precision);
-    return ny >= pts ? 1 : std::min(pts / ny, nx / 2 + 1);
+    const int pts = (ny >= 1024 ? COL_BUDGET / 4 : COL_BUDGET / 2) / sk_elem(precision);
+    return ny >= pts ? 1 : std::min(pts / ny, nx / 2);   // a power of two
 }
 
 hipError_t set_sk_lds_limits(int precision, int G, int max_row, int max_col)
