@@ -696,11 +696,14 @@ void radial_metric(int nx, int ny, int *P, int *xwide, int *nbins)
     *nbins = (int)((s + *P) / (2 * *P)) + 1;
 }
 
-// Two-step launch shapes to time: widths 512, 256, 384, 448 (256 first for a population buffer of
-// more than 1 GiB) with tiles of 32, 16 and 64 rows,
-// and for each width the tile heights whose workgroup lists just fill 2, 3, 4 or 6 rounds of the
-// workgroups resident at once (a launch whose last round is partly empty leaves CUs idle while it
-// drains; at 8192^2 and 256 lanes, 89-row tiles, three rounds: 2% faster than 32-row ones).
+// Two-step launch shapes to time: widths 512 and 256 (256 first for a population buffer of more than
+// 1 GiB), 384 and 448 where a replica's row fits one of them but not 256 (a whole row loses no columns;
+// as strips those widths, without a kernel of fixed width, ran 20-40% slower at every size), with tiles of
+// 32, 16 and 64 rows, and for each width the tile heights whose workgroup lists just fill 1, 2, 3, 4 or 6
+// rounds of the workgroups resident at once (a launch whose last round is partly empty leaves CUs idle
+// while it drains; at 8192^2 and 256 lanes, 89-row tiles, three rounds: 2% faster than 32-row ones; at
+// 2048^2 19-row tiles, one round: 49.6-51.4 us per step, 18 rows, two workgroups over a round, 61.3, 10
+// rows 54.6, 24 rows 56.5).
 std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
 {
     std::vector<std::pair<int, int>> shapes;
@@ -722,7 +725,10 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
     // and for those large states the 256-lane strips come first: over 600 steps of the 8192^2
     // lattice on one MI355X, 256 x 67 and 256 x 32 tiles ran 0.630 and 0.631 ms per step, every
     // 512-lane shape 0.638-0.657, while the short trials ranked 512 x 92 within 1% of them
-    const std::vector<int> widths = fill_first ? std::vector<int>{256, 512, 384, 448} : std::vector<int>{512, 256, 384, 448};
+    std::vector<int> widths = fill_first ? std::vector<int>{256, 512} : std::vector<int>{512, 256};
+    for (int bx : {384, 448})
+        if (std::any_of(h->reps.begin(), h->reps.end(), [bx](const RepDesc &d) { return d.nx > 256 && d.nx <= bx; }))
+            widths.push_back(bx);
     for (int bx : widths) {
         std::vector<int> heights;
         if (!fill_first) heights = {32, 16, 64};
@@ -734,7 +740,7 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
             *slots = (long long)step2_blocks_per_cu(h->precision, plain, cn, bx, gmax) * ncu;
             return (long long)w.size() - 1;
         };
-        for (int r : {4, 3, 6, 2}) {
+        for (int r : {4, 3, 6, 2, 1}) {
             if (ncu == 0) break;
             // the smallest height whose list fits r rounds (the count falls as the height grows)
             int lo = STEP2_MIN_H, hi = std::max(STEP2_MIN_H, max_ny);
@@ -754,6 +760,27 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
         for (int rows : heights) shapes.push_back({bx, rows});
     }
     return shapes;
+}
+
+// Below the sizes that are tuned by timing, one lattice of at least 5/4 2^21 nodes takes the two-step
+// kernel too, in 256-lane strips and the lowest tiles whose workgroups are all resident at once, unless its
+// last strip would leave over a fifth of the strips' columns empty; 0: k_tile.  us per step, k_tile / that:
+// FP32 1450^2 28.5 / 29.1, 1600^2 33.4 / 32.4, 1750^2 39.4 / 34.8, 2000^2 54.9 / 45.0, 300 x 12000 (two
+// strips for 300 columns) 46.8 / 62.1; FP64 1450^2 63.6 / 61.7, 1750^2 89.3 / 78.6, 2000^2 113 / 101.
+int step2_one_round_rows(const lb_handle *h)
+{
+    constexpr int bx = 256, w = bx - 6;
+    if (h->n_rep != 1 || h->L.nodes < 5ll << 19) return 0;
+    const int nx = h->reps[0].nx, ny = h->reps[0].ny, strips = (nx + w - 1) / w;
+    if (nx <= bx || 5ll * nx < 4ll * strips * w) return 0;
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    const int slots = ncu * step2_blocks_per_cu(h->precision, h->precision == LB_FP32, !h->cn_reps.empty(), bx, 1);
+    const int bands = slots / strips;
+    if (bands < 1) return 0;
+    return std::max(STEP2_MIN_H, (ny + bands - 1) / bands);
 }
 
 // time a few steps of each candidate launch shape and keep the fastest: for k_step (one step
@@ -786,7 +813,15 @@ lb_status autotune(lb_handle *h)
     int tns = 0, tty = 0;
     const char *tile_env = getenv("LBF_NODE_TILE");
     const bool pint = tile_env && sscanf(tile_env, "%d,%d", &tns, &tty) == 2;
-    if (pint || (h->L.nodes < (1ll << 22) && !pin1 && !pin2 && !force_k)) {
+    const bool small = h->L.nodes < (1ll << 22) && !pin1 && !pin2 && !force_k;
+    const int one_round = small && !pint ? step2_one_round_rows(h) : 0;
+    if (one_round) {
+        lb_status st = set_tiles(h, 256, 8);
+        if (st == LB_OK) st = set_tiles2(h, 256, one_round);
+        h->k = 2;
+        return st;
+    }
+    if (pint || small) {
         if (!pint) node_tile_shape(h, &tns, &tty);
         lb_status st = set_node_tiles(h, 0, tns, tty);
         if (st == LB_OK) st = set_node_tiles(h, 1, 1, TILE_ONE_STEP_TY);

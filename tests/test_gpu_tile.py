@@ -80,3 +80,23 @@ def test_impossible_node_tiles_are_refused(monkeypatch, tile):
     monkeypatch.setenv("LBF_NODE_TILE", tile)
     with pytest.raises(L.LbError):
         L.Lattice(W.single_phase(64, 64, kT=1e-5, seed=1), precision="fp32s")
+
+
+@pytest.mark.parametrize("shape", [(1700, 1600), (5200, 520), (300, 9000)], ids=["1700x1600", "5200x520", "300x9000"])
+@pytest.mark.parametrize("precision", [2, 0])
+def test_middle_sizes_bitwise(monkeypatch, shape, precision):
+    """2.7 million nodes, about where a lattice goes from the lane-per-node tiles to one round of the
+    two-step kernel's strips (not when a strip would be mostly empty)."""
+    from paper_1009_0254_amd import lbfluct as L
+    cfg = W.single_phase(*shape, kT=1e-5, seed=9)
+    got = []
+    for env in ({}, {"LBF_TILE": "256,16", "LBF_STEPS_PER_LAUNCH": "1"}):
+        for k in ("LBF_TILE", "LBF_TILE2", "LBF_STEPS_PER_LAUNCH", "LBF_NODE_TILE"):
+            monkeypatch.delenv(k, raising=False)
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        lat = L.Lattice(cfg, precision=precision)
+        lat.step(35)
+        got.append(lat.lb_moments(0)[0])
+        lat.close()
+    assert torch.equal(*got)
