@@ -111,6 +111,46 @@ template <typename U> __device__ __forceinline__ void moments9(const U g[9], U m
 
 constexpr int SK_CACHE_PAIRS = 4;   // node pairs per lane whose moments stay in registers
 
+// Two adjacent stored values, one load: half the requests of the row kernels, whose lanes hold node pairs
+// (one sample, 8192^2: 3.85 -> 3.59 ms, 4096^2 1.08 -> 0.97 ms, 2048^2 FP64 415 -> 391 us; aligned to one value only: x - 1 and x + 1 are odd)
+template <typename S> struct __attribute__((packed, aligned(sizeof(S)))) SkTwo {
+    S a, b;
+};
+template <typename S> __device__ __forceinline__ SkTwo<S> load_two(const S *p) { return *reinterpret_cast<const SkTwo<S> *>(p); }
+
+// load_pull of nodes (x, y) and (x + 1, y), x even: nine loads of two values (and the wrapped values of
+// a row's first and last pair)
+template <typename S>
+__device__ __forceinline__ void load_pull_pair(const S *__restrict__ P, int nx, int ny, int x, int y, S u[9], S v[9])
+{
+    const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+    const int cx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1}, yr[9] = {y, y, ym, y, yp, ym, ym, yp, yp};
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        const S *row = P + pop_at(nx, i, 0, yr[i]);
+        const int x0 = cx[i] == 1 ? max(x - 1, 0) : cx[i] == -1 ? min(x + 1, nx - 2) : x;
+        const SkTwo<S> q = load_two(row + x0);
+        u[i] = q.a;
+        v[i] = q.b;
+    }
+    if (x == 0) {   // (nx - 1, 0) where (0, 1) was loaded
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            if (cx[i] == 1) {
+                v[i] = u[i];
+                u[i] = P[pop_at(nx, i, nx - 1, yr[i])];
+            }
+    }
+    if (x == nx - 2) {   // (nx - 1, 0) where (nx - 2, nx - 1) was loaded
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            if (cx[i] == -1) {
+                u[i] = v[i];
+                v[i] = P[pop_at(nx, i, 0, yr[i])];
+            }
+    }
+}
+
 // The nine moments of nodes (x, y) and (x + 1, y) relative to those of the reference, in Tt,
 // packed as (even, odd) complex pairs: the differences of the pulled values come first (for
 // values of one population they are exact or rounded at the fluctuation's own scale), then
@@ -120,8 +160,7 @@ __device__ __forceinline__ void pair_moments(const S *__restrict__ P, int nx, in
                                              const Tt *vref, typename V2<Tt>::type m[9])
 {
     S v[2][9];
-    load_pull(P, nx, ny, x, y, v[0]);
-    load_pull(P, nx, ny, x + 1, y, v[1]);
+    load_pull_pair(P, nx, ny, x, y, v[0], v[1]);
     Tt de[9], dd[9], me[9], mo[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
@@ -239,7 +278,7 @@ __global__ void __launch_bounds__(SK_REF_THREADS)
 // SK_CACHE_PAIRS) are pulled once and their nine moments kept in registers for all mode
 // groups, which are GC modes each and fixed at compile time (so that a placed group's
 // registers are free for the transforms); otherwise each group of G modes pulls the row
-// again (the repeats hit L2 or the MALL).  OWNREF: every block forms its replica's reference itself
+// again (the repeats hit L2 or the MALL; GC = 1: mode 0 alone, for the snapshot).  OWNREF: every block forms its replica's reference itself
 // (blocks of SK_REF_THREADS lanes; the same sums in the same order) instead of reading k_sk_ref's,
 // and the replica's first block stores it for the column pass.
 template <typename S, typename Tt, int RMAX, bool CACHE, int GC, bool OWNREF = false>
@@ -317,9 +356,13 @@ __global__ void __launch_bounds__(SK_THREADS)
                 C m[9];
                 pair_moments(P, nx, ny, 2 * n, y0 + rr, vref, m);
                 const unsigned jb = bitrev((unsigned)n, logM);
+                if constexpr (GC == 1) {   // mode 0 alone: the compiler drops the other moments
+                    X[lds_at(rr * M + jb, sh)] = m[0];
+                } else {
 #pragma unroll
-                for (int c = 0; c < 9; ++c)
-                    if (c >= a0 && c < a0 + gcount) X[lds_at((((c - a0) << lRp) + rr) * M + jb, sh)] = m[c];
+                    for (int c = 0; c < 9; ++c)
+                        if (c >= a0 && c < a0 + gcount) X[lds_at((((c - a0) << lRp) + rr) * M + jb, sh)] = m[c];
+                }
             }
         }
         __syncthreads();
@@ -508,24 +551,37 @@ __device__ __forceinline__ long long ceil_root(long long v, long long m)
 // = sqrt(R2) / P, and k lies in shell b = floor(sqrt(R2) / P + 1/2), i.e.
 // ((2b - 1) P)^2 <= 4 R2 < ((2b + 1) P)^2.  Means over the full k plane without k = 0;
 // the half plane stands for its mirror image with weight 2 except at kx = 0 and nx/2.
-__global__ void __launch_bounds__(256) k_sk_bins(const double *__restrict__ plane, int nx, int ny, int P, int xwide,
-                                                 int nbins, double *__restrict__ out)
+//
+// Two passes, each sum in a fixed order.  k_sk_bins: a block takes SK_BIN_SHELLS adjacent shells and a
+// range of columns kx, SK_BIN_COLS of them at a time: the lanes of one column hold adjacent shells, whose
+// intervals of ky follow each other, so that they read whole cache lines.  k_sk_bins_sum adds the ranges'
+// partial sums.  With one shell per block each lane's reads were a line of their own: 1.83 ms at 16384^2
+// (1.1 GB), now 0.54 ms.  (A shell per lane walking its columns: 1.64 ms, and 6 times slower than a block
+// per shell at 2048^2, for the lanes whose shell touches the column tangentially.)
+constexpr int SK_BIN_SHELLS = 16, SK_BIN_COLS = 16, SK_SUM_SHELLS = 64, SK_SUM_PARTS = 8;
+// ranges of columns, of one pass each up to 32 ranges
+int sk_bin_ranges(int nh) { return std::min(32, (nh + SK_BIN_COLS - 1) / SK_BIN_COLS); }
+
+__global__ void __launch_bounds__(SK_BIN_SHELLS *SK_BIN_COLS)
+    k_sk_bins(const double *__restrict__ plane, int nx, int ny, int P, int xwide, int nbins, int cols,
+              double *__restrict__ part)
 {
-    __shared__ double ss[256], sc[256];
-    const int b = blockIdx.x;
+    __shared__ double ss[SK_BIN_COLS][SK_BIN_SHELLS], sc[SK_BIN_COLS][SK_BIN_SHELLS];
+    const int l = threadIdx.x % SK_BIN_SHELLS, j = threadIdx.x / SK_BIN_SHELLS, b = blockIdx.x * SK_BIN_SHELLS + l;
     const long long wx = xwide ? 1 : (long long)P * P, wy = xwide ? (long long)P * P : 1;
     const long long lo = b > 0 ? (long long)(2 * b - 1) * P * (2 * b - 1) * P : 0;
     const long long hi = (long long)(2 * b + 1) * P * (2 * b + 1) * P;
     const int hx = nx / 2, hy = ny / 2;
+    const int kx1 = min((int)(blockIdx.y + 1) * cols, hx + 1);
     double s = 0, c = 0;
-    for (int kx = threadIdx.x; kx <= hx; kx += blockDim.x) {
+    for (int kx = blockIdx.y * cols + j; kx < kx1; kx += SK_BIN_COLS) {
         const long long ax = 4 * wx * (long long)kx * kx;
         if (ax >= hi) break;
-        const long long y0 = ceil_root(lo - ax, 4 * wy);
-        const long long y1 = min(ceil_root(hi - ax, 4 * wy), (long long)hy + 1);
+        const int y0 = (int)min(ceil_root(lo - ax, 4 * wy), (long long)hy + 1);
+        const int y1 = (int)min(ceil_root(hi - ax, 4 * wy), (long long)hy + 1);
         const double w = (kx == 0 || kx == hx) ? 1.0 : 2.0;
         const double *D = plane + (long long)kx * ny;
-        for (long long ky = y0; ky < y1; ++ky) {
+        for (int ky = y0; ky < y1; ++ky) {
             if (kx == 0 && ky == 0) continue;
             s += w * D[ky];
             c += w;
@@ -535,32 +591,67 @@ __global__ void __launch_bounds__(256) k_sk_bins(const double *__restrict__ plan
             }
         }
     }
-    ss[threadIdx.x] = s;
-    sc[threadIdx.x] = c;
+    ss[j][l] = s;
+    sc[j][l] = c;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            ss[threadIdx.x] += ss[threadIdx.x + h];
-            sc[threadIdx.x] += sc[threadIdx.x + h];
+    for (int h = SK_BIN_COLS / 2; h > 0; h >>= 1) {
+        if (j < h) {
+            ss[j][l] += ss[j + h][l];
+            sc[j][l] += sc[j + h][l];
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        out[b] = sc[0] > 0 ? ss[0] / sc[0] : 0.0;
-        out[nbins + b] = sc[0];
+    if (j == 0 && b < nbins) {
+        part[(long long)blockIdx.y * 2 * nbins + b] = ss[0][l];
+        part[(long long)blockIdx.y * 2 * nbins + nbins + b] = sc[0][l];
     }
 }
 
-__global__ void k_sk_read(const double *__restrict__ acc, double *__restrict__ out, int nx, int ny, double inv_ns)
+// SK_SUM_PARTS lanes per shell take every SK_SUM_PARTS-th partial sum, then add up in order
+__global__ void __launch_bounds__(SK_SUM_SHELLS *SK_SUM_PARTS)
+    k_sk_bins_sum(const double *__restrict__ part, int nparts, int nbins, double *__restrict__ out)
 {
-    const int nh = nx / 2 + 1;
-    const long long per = (long long)nh * ny;
-    const long long total = 9 * per;
-    for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < total; k += (long long)gridDim.x * blockDim.x) {
-        const long long a = k / per, rem = k - a * per;
-        const long long ky = rem / nh, kx = rem - ky * nh;
-        out[k] = acc[a * per + kx * ny + ky] * inv_ns;
+    __shared__ double ss[SK_SUM_PARTS][SK_SUM_SHELLS], sc[SK_SUM_PARTS][SK_SUM_SHELLS];
+    const int l = threadIdx.x % SK_SUM_SHELLS, q = threadIdx.x / SK_SUM_SHELLS, b = blockIdx.x * SK_SUM_SHELLS + l;
+    double s = 0, c = 0;
+    if (b < nbins)
+        for (int j = q; j < nparts; j += SK_SUM_PARTS) {
+            s += part[(long long)j * 2 * nbins + b];
+            c += part[(long long)j * 2 * nbins + nbins + b];
+        }
+    ss[q][l] = s;
+    sc[q][l] = c;
+    __syncthreads();
+    if (q == 0 && b < nbins) {
+        for (int j = 1; j < SK_SUM_PARTS; ++j) {
+            s += ss[j][l];
+            c += sc[j][l];
+        }
+        out[b] = c > 0 ? s / c : 0.0;
+        out[nbins + b] = c;
     }
+}
+
+// Mean spectra for the caller: acc [nh][ny] to out [ny][nh] per mode, scaled.  Bound by HBM (16 B per value);
+// read and written along the lines of each side through a tile of RT x RT in LDS (one slot of padding, so
+// that a column read touches every bank).  A lane per output with the reads ny apart took 2.20 ms at 8192^2
+// (4.8 GB), this 0.94 ms.
+constexpr int RT = 32, READ_ROWS = 8;
+__global__ void __launch_bounds__(RT * READ_ROWS) k_sk_read(const double *__restrict__ acc, double *__restrict__ out,
+                                                            int nh, int ny, double inv_ns)
+{
+    __shared__ double tile[RT][RT + 1];
+    const long long per = (long long)nh * ny;
+    const double *A = acc + blockIdx.z * per;
+    double *O = out + blockIdx.z * per;
+    const int ky0 = blockIdx.x * RT, kx0 = blockIdx.y * RT, tx = threadIdx.x % RT, ty = threadIdx.x / RT;
+#pragma unroll
+    for (int j = ty; j < RT; j += READ_ROWS)
+        if (kx0 + j < nh && ky0 + tx < ny) tile[j][tx] = A[(long long)(kx0 + j) * ny + ky0 + tx];
+    __syncthreads();
+#pragma unroll
+    for (int j = ty; j < RT; j += READ_ROWS)
+        if (ky0 + j < ny && kx0 + tx < nh) O[(long long)(ky0 + j) * nh + kx0 + tx] = tile[tx][j] * inv_ns;
 }
 
 // radix of the in-LDS passes: 8, except 4 for the FP64 column transforms (at 8 their
@@ -599,8 +690,13 @@ hipError_t launch_rows(int precision, const SkLaunch &a, int a_first, int a_coun
     // registers across the mode groups (FP64 would spill)
     const bool cache = precision != 0 && a_first == 0 && a_count == 9 && G == 4 &&
                        a.lds_rows / 2 <= SK_CACHE_PAIRS * threads;
-    if (precision == 0)
+    const bool rho = a_first == 0 && a_count == 1;
+    if (precision == 0 && rho)
+        rows_kernel<double, double, SK_ROW_RADIX<double>, false, 1>(a, a_first, a_count, G, threads, s);
+    else if (precision == 0)
         rows_kernel<double, double, SK_ROW_RADIX<double>, false>(a, a_first, a_count, G, threads, s);
+    else if (rho)
+        rows_kernel<float, float, SK_ROW_RADIX<float>, false, 1>(a, a_first, a_count, G, threads, s);
     else if (cache)
         rows_kernel<float, float, SK_ROW_RADIX<float>, true, 4>(a, a_first, a_count, G, threads, s);
     else
@@ -633,6 +729,7 @@ template <typename S, typename Tt> hipError_t lds_limits_of(size_t rows, size_t 
 {
     hipError_t e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, false, 0>, rows);
     if (e == hipSuccess) e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, false, 0, true>, rows);
+    if (e == hipSuccess) e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, false, 1>, rows);
     if constexpr (sizeof(Tt) == 4) {   // the register-cached row variant exists for FP32 only
         if (e == hipSuccess) e = lds_limit(k_sk_rows<S, Tt, SK_ROW_RADIX<Tt>, true, 4>, rows);
     }
@@ -697,17 +794,23 @@ hipError_t launch_sk_snapshot(int precision, const SkLaunch &a, int nx, int ny, 
     else
         cols_kernel<float, true>(precision, a, 1, plane, s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sk_bins, dim3((unsigned)nbins), dim3(256), 0, s, (const double *)plane, nx, ny, P, xwide,
-                       nbins, out);
+    // the partial sums follow in slot 2: at most nh / 16 + 1 ranges of 2 nbins doubles, nbins <= 0.71 min(nx, ny)
+    // + 2 (a slot has ny elements of at least 8 bytes for each of the nh columns, padded to a multiple of 16)
+    double *part = (double *)((char *)a.spec + (size_t)sk_elem(precision) * 2 * a.Ptot);
+    const int nh = nx / 2 + 1, ranges = sk_bin_ranges(nh), per = (nh + ranges - 1) / ranges;
+    const int cols = (per + SK_BIN_COLS - 1) / SK_BIN_COLS * SK_BIN_COLS;
+    hipLaunchKernelGGL(k_sk_bins, dim3((unsigned)((nbins + SK_BIN_SHELLS - 1) / SK_BIN_SHELLS), (unsigned)ranges),
+                       dim3(SK_BIN_SHELLS * SK_BIN_COLS), 0, s, (const double *)plane, nx, ny, P, xwide, nbins, cols, part);
+    hipLaunchKernelGGL(k_sk_bins_sum, dim3((unsigned)((nbins + SK_SUM_SHELLS - 1) / SK_SUM_SHELLS)),
+                       dim3(SK_SUM_SHELLS * SK_SUM_PARTS), 0, s, (const double *)part, ranges, nbins, out);
     return hipGetLastError();
 }
 
 hipError_t launch_sk_read(const double *acc, double *out, int nx, int ny, double inv_ns, hipStream_t s)
 {
-    const long long total = 9ll * (nx / 2 + 1) * ny;
-    long long g = (total + 255) / 256;
-    if (g > 65536) g = 65536;
-    hipLaunchKernelGGL(k_sk_read, dim3((unsigned)g), dim3(256), 0, s, acc, out, nx, ny, inv_ns);
+    const int nh = nx / 2 + 1;
+    const dim3 grid((unsigned)((ny + RT - 1) / RT), (unsigned)((nh + RT - 1) / RT), 9);
+    hipLaunchKernelGGL(k_sk_read, grid, dim3(RT * READ_ROWS), 0, s, acc, out, nh, ny, inv_ns);
     return hipGetLastError();
 }
 
