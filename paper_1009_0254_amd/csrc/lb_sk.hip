@@ -218,6 +218,14 @@ __device__ __forceinline__ int sk_fill_pair(int e, bool whole64)
     return whole64 ? (e & ~63) | ((e & 15) << 2) | ((e >> 4) & 3) : e;
 }
 
+// The FP32 columns' fill: lane e reads ky = sk_fill_y(e).  Pairs of lanes read adjacent ky (in one cache
+// line of the spectra's chunks), the pairs in bit-reversed order, so that their LDS slots bitrev(ky)
+// run in order, half a transform apart within a pair.
+__device__ __forceinline__ int sk_fill_y(int e, int logn)
+{
+    return ((int)bitrev((unsigned)(e >> 1), logn - 1) << 1) | (e & 1);
+}
+
 constexpr int SK_REF_THREADS = 256;
 
 // The reference of replica r: the mean over row 0 of each pulled population, in FP64 with a
@@ -446,9 +454,8 @@ __global__ void __launch_bounds__(SK_THREADS)
     // added to the real part of output 0 of this block when that output is k = 0
     const double k0 = kx0 == 0 && par == 0 ? (double)q.nx * (double)ny * base[18 * r + a] : 0.0;
     const int L = ny / split, logL = q.logny - (split - 1);
-    // P16 (FP32): the 1/16-pad layout, filled in destination order (lane e writes slot e of the
-    // bit-reversed line and reads its source at bitrev(e)), the remainder pass last; FP64 keeps
-    // the wide pad and a source-ordered fill
+    // P16 (FP32): the 1/16-pad layout, filled nearly in destination order (sk_fill_y), the
+    // remainder pass last; FP64 keeps the wide pad and a source-ordered fill
     constexpr bool P16 = sizeof(Tt) == 4;
     const int sh = P16 ? LDS_PAD16 : lds_pad_shift(logL);
     if (split == 1) {
@@ -472,12 +479,12 @@ __global__ void __launch_bounds__(SK_THREADS)
                 C v[4];
                 for (int u = 0; u < 4; ++u) {
                     const int e = min(e0 + u * (int)blockDim.x, tot - 1);
-                    const int y = (int)bitrev((unsigned)(e & (L - 1)), logL);
-                    v[u] = S0[sk_at32(y, kx0 + (e >> logL), ny)];
+                    v[u] = S0[sk_at32(sk_fill_y(e & (L - 1), logL), kx0 + (e >> logL), ny)];
                 }
                 for (int u = 0; u < 4; ++u) {
                     const int e = e0 + u * (int)blockDim.x;
-                    if (e < tot) X[lds_at(e, sh)] = v[u];
+                    const int y = sk_fill_y(e & (L - 1), logL);
+                    if (e < tot) X[lds_at((e & ~(L - 1)) | (int)bitrev((unsigned)y, logL), sh)] = v[u];
                 }
             }
         } else {
@@ -500,9 +507,9 @@ __global__ void __launch_bounds__(SK_THREADS)
         // X_{2k+p} = sum_n [x_n + (-1)^p x_{n+L}] W^{pn} exp(-2 pi i n k / L), W = exp(-2 pi i / ny)
         const int wstride = nmax / ny;
         for (int r = threadIdx.x; r < L; r += blockDim.x) {
-            const int n = P16 ? (int)bitrev((unsigned)r, logL) : r;
+            const int n = P16 ? sk_fill_y(r, logL) : r;
             const C u = S0[sk_at32(n, kx0, ny)], v = S0[sk_at32(n + L, kx0, ny)];
-            X[lds_at(P16 ? r : (int)bitrev((unsigned)n, logL), sh)] =
+            X[lds_at((int)bitrev((unsigned)n, logL), sh)] =
                 par == 0 ? cadd(u, v) : cmul(csub(u, v), twiddle(T, n * wstride));
         }
     }
@@ -795,7 +802,7 @@ hipError_t launch_sk_snapshot(int precision, const SkLaunch &a, int nx, int ny, 
         cols_kernel<float, true>(precision, a, 1, plane, s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the partial sums follow in slot 2: at most nh / 16 + 1 ranges of 2 nbins doubles, nbins <= 0.71 min(nx, ny)
-    // + 2 (a slot has ny elements of at least 8 bytes for each of the nh columns, padded to a multiple of 16)
+    // + 2 (a slot has ny elements of at least 8 bytes for each of the nh columns, padded to a multiple of 8)
     double *part = (double *)((char *)a.spec + (size_t)sk_elem(precision) * 2 * a.Ptot);
     const int nh = nx / 2 + 1, ranges = sk_bin_ranges(nh), per = (nh + ranges - 1) / ranges;
     const int cols = (per + SK_BIN_COLS - 1) / SK_BIN_COLS * SK_BIN_COLS;

@@ -9,7 +9,7 @@ namespace lbf {
 // complex values, so that the column pass reads each chunk's rows as one contiguous run (a
 // plain [ky][nh] layout puts consecutive ky of one kx a row apart and every read in another
 // HBM page).  nh = nx/2 + 1 is padded to a multiple of SK_KG.
-constexpr int SK_KG = 16;
+constexpr int SK_KG = 8;
 __host__ __device__ inline long long sk_nh_padded(int nx) { return (long long)((nx / 2 + SK_KG) / SK_KG) * SK_KG; }
 __host__ __device__ inline long long sk_at(int ky, int kx, int ny)
 {
