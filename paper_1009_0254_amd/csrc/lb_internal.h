@@ -177,7 +177,10 @@ hipError_t launch_init(int precision, void *f, double *rho_tmp, const RepDesc *d
                        const RepDesc &h_rep, int rep_index, hipStream_t s);
 hipError_t launch_moments(int precision, const void *f, const RepDesc *d_reps, const RepDesc &h_rep,
                           int rep_index, double *d_m9, double *partials, int nblocks, double *d_tot,
-                          hipStream_t s);
+                          hipEvent_t done, hipStream_t s);
+// the totals from the partial sums of launch_moments: its second kernel when d_tot is given, or this, bit for bit
+// the same; done (or nullptr): an event that the first kernel completes itself
+void reduce_partials(const double *partials, int nblocks, double tot[6]);
 hipError_t launch_normals(uint64_t seed, uint32_t replica, uint64_t t, int64_t n, int precision,
                           double *d_out, hipStream_t s);
 hipError_t launch_philox(uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1, int64_t n,
@@ -242,7 +245,7 @@ hipError_t launch_sk_sample(int precision, const SkLaunch &a, hipStream_t s);
 // (means) and out[nbins..2 nbins) (counts); P, xwide describe the bin metric
 hipError_t launch_sk_snapshot(int precision, const SkLaunch &a, int nx, int ny, int nbins, int P, int xwide,
                               double *out, hipStream_t s);
-hipError_t launch_sk_read(const double *acc, double *out, int nx, int ny, double inv_ns, hipStream_t s);
+hipError_t launch_sk_read(const double *acc, double *out, int nx, int ny, double inv_ns, hipEvent_t done, hipStream_t s);
 hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t s);
 
 }  // namespace lbf

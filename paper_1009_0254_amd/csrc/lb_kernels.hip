@@ -19,6 +19,7 @@
 #include "lb_internal.h"
 #include "lb_rng.h"
 
+#include <hip/hip_ext.h>
 #include <math.h>
 
 namespace lbf {
@@ -449,16 +450,32 @@ hipError_t launch_init(int precision, void *f, double *rho_tmp, const RepDesc *d
 }
 
 hipError_t launch_moments(int precision, const void *f, const RepDesc *d_reps, const RepDesc &h_rep, int rep_index,
-                          double *d_m9, double *partials, int nblocks, double *d_tot, hipStream_t s)
+                          double *d_m9, double *partials, int nblocks, double *d_tot, hipEvent_t done, hipStream_t s)
 {
     if (precision == 0)
-        hipLaunchKernelGGL(k_moments<double>, dim3(nblocks), dim3(RED_THREADS), 0, s, (const double *)f, d_reps,
-                           rep_index, d_m9, partials);
+        hipExtLaunchKernelGGL(k_moments<double>, dim3(nblocks), dim3(RED_THREADS), 0, s, nullptr, done, 0,
+                              (const double *)f, d_reps, rep_index, d_m9, partials);
     else
-        hipLaunchKernelGGL(k_moments<float>, dim3(nblocks), dim3(RED_THREADS), 0, s, (const float *)f, d_reps,
-                           rep_index, d_m9, partials);
-    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(RED_THREADS), 0, s, partials, nblocks, d_tot);
+        hipExtLaunchKernelGGL(k_moments<float>, dim3(nblocks), dim3(RED_THREADS), 0, s, nullptr, done, 0,
+                              (const float *)f, d_reps, rep_index, d_m9, partials);
+    if (d_tot) hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(RED_THREADS), 0, s, partials, nblocks, d_tot);
     return hipGetLastError();
+}
+
+// k_reduce_partials on the host: the same additions in the same order
+void reduce_partials(const double *partials, int nblocks, double tot[6])
+{
+    double red[RED_THREADS][6];
+    for (int t = 0; t < RED_THREADS; ++t) {
+        double acc[6] = {0, 0, 0, 0, 0, 0};
+        for (int b = t; b < nblocks; b += RED_THREADS)
+            for (int c = 0; c < 6; ++c) acc[c] += partials[b * 6 + c];
+        for (int c = 0; c < 6; ++c) red[t][c] = acc[c];
+    }
+    for (int s = RED_THREADS / 2; s > 0; s >>= 1)
+        for (int t = 0; t < s; ++t)
+            for (int c = 0; c < 6; ++c) red[t][c] += red[t + s][c];
+    for (int c = 0; c < 6; ++c) tot[c] = red[0][c];
 }
 
 hipError_t launch_normals(uint64_t seed, uint32_t replica, uint64_t t, int64_t n, int precision, double *d_out,

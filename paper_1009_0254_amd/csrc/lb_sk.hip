@@ -29,6 +29,8 @@
 // eigenvalues) reuses 1-3 for mode 0 of one replica and bins |rho(k)|^2 / n with integer
 // shell arithmetic.
 
+#include <hip/hip_ext.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -813,11 +815,11 @@ hipError_t launch_sk_snapshot(int precision, const SkLaunch &a, int nx, int ny, 
     return hipGetLastError();
 }
 
-hipError_t launch_sk_read(const double *acc, double *out, int nx, int ny, double inv_ns, hipStream_t s)
+hipError_t launch_sk_read(const double *acc, double *out, int nx, int ny, double inv_ns, hipEvent_t done, hipStream_t s)
 {
     const int nh = nx / 2 + 1;
     const dim3 grid((unsigned)((ny + RT - 1) / RT), (unsigned)((nh + RT - 1) / RT), 9);
-    hipLaunchKernelGGL(k_sk_read, grid, dim3(RT * READ_ROWS), 0, s, acc, out, nh, ny, inv_ns);
+    hipExtLaunchKernelGGL(k_sk_read, grid, dim3(RT * READ_ROWS), 0, s, nullptr, done, 0, acc, out, nh, ny, inv_ns);
     return hipGetLastError();
 }
 
