@@ -523,7 +523,7 @@ lb_status set_tiles2(lb_handle *h, int bx, double rows)
 {
     std::vector<Tile> t;
     std::vector<int32_t> w;
-    const int gmax = make_tiles2(h->reps, bx, rows, t, w);
+    const int gmax = make_tiles2(h->reps, (int)elem_size(h->precision), bx, rows, t, w);
     if ((long long)t.size() > h->L.max_tiles2) return LB_EINVAL;
     if (hipMemcpyAsync(h->tiles2_d, t.data(), sizeof(Tile) * t.size(), hipMemcpyHostToDevice, h->stream) != hipSuccess ||
         hipMemcpyAsync(h->wgs2_d, w.data(), sizeof(int32_t) * w.size(), hipMemcpyHostToDevice, h->stream) !=
@@ -784,7 +784,7 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
         auto counts = [&](int rows, long long *slots) {
             std::vector<Tile> t;
             std::vector<int32_t> w;
-            const int gmax = make_tiles2(h->reps, bx, rows, t, w);
+            const int gmax = make_tiles2(h->reps, (int)elem_size(h->precision), bx, rows, t, w);
             *slots = (long long)step2_blocks_per_cu(h->precision, plain, cn, bx, gmax) * ncu;
             return (long long)w.size() - 1;
         };
@@ -817,7 +817,8 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
 // strips for 300 columns) 46.8 / 62.1; FP64 1450^2 63.6 / 61.7, 1750^2 89.3 / 78.6, 2000^2 113 / 101.
 int step2_one_round_rows(const lb_handle *h)
 {
-    constexpr int bx = 256, w = bx - 6;
+    constexpr int bx = 256;
+    const int w = step2_out(bx, (int)elem_size(h->precision));
     if (h->n_rep != 1 || h->L.nodes < 5ll << 19) return 0;
     const int nx = h->reps[0].nx, ny = h->reps[0].ny, strips = (nx + w - 1) / w;
     if (nx <= bx || 5ll * nx < 4ll * strips * w) return 0;

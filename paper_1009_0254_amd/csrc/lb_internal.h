@@ -111,7 +111,7 @@ std::vector<Tile> make_tiles(const std::vector<RepDesc> &reps, int bx, double h)
 
 // Two steps per launch (lb_step2.hip).  A workgroup of bx lanes holds G lane groups of bx / G
 // lanes, each running one tile: workgroup w runs tiles[wgs[w] .. wgs[w + 1]), G = their
-// count.  A tile's x0 is its first output column (strips of bx / G - 6 output columns); a
+// count.  A tile's x0 is its first output column (strips of step2_out columns); a
 // replica whose row fits a group (nx <= bx / G) has x0 = 0 and whole-row tiles; rep < 0
 // marks an empty group.
 struct Step2Launch {
@@ -131,9 +131,19 @@ struct Step2Launch {
     int32_t plain;
 };
 constexpr int STEP2_MIN_BX = 128, STEP2_MIN_H = 8;
+// Columns that a strip of bx lanes stores: bx - 6 at most, and in FP32 from 256 lanes on a multiple of 64
+// bytes, so that neighbouring strips, which reach a row at different times, share no 64-byte line of it: with
+// 250 columns every row of every population had such a line written twice, in parts.  us per step, 250 / 240
+// columns (64 bytes) / 224 (128 bytes): 8192^2 630 / 614 / 642, without noise 635 / 546 / 545, 4096^2
+// 185 / 171 / 179.  FP64, not bound by memory, gains nothing (8192^2 without noise 1060 / 1058) and takes a
+// strip more.  Narrower strips keep bx - 6: 10 of 122 columns would be lost.
+__host__ __device__ constexpr int step2_out(int bx, int elem)
+{
+    return bx >= 256 && elem == 4 ? (bx - 6) / 16 * 16 : bx - 6;
+}
 // tiles and workgroup prefix of the two-step kernel for workgroups of bx lanes and tiles of
 // about h rows; returns the largest group count
-int make_tiles2(const std::vector<RepDesc> &reps, int bx, double h, std::vector<Tile> &tiles,
+int make_tiles2(const std::vector<RepDesc> &reps, int elem, int bx, double h, std::vector<Tile> &tiles,
                 std::vector<int32_t> &wgs);
 // upper bound of the tile count of make_tiles2 for any bx >= STEP2_MIN_BX, h >= STEP2_MIN_H
 long long max_tiles2(const std::vector<int> &nx, const std::vector<int> &ny);
