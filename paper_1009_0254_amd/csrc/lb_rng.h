@@ -203,7 +203,7 @@ template <> struct Gauss<float> {
     static __device__ __forceinline__ void pair(uint32_t be, uint32_t bo, float &a, float &b)
     {
 #pragma clang fp contract(on)
-        const float ue = ((float)be + 0.5f) * 0x1p-21f;
+        const float ue = __builtin_fmaf((float)be, 0x1p-21f, 0x1p-22f);   // (be + 1/2) 2^-21, exact
         const float uo = turn21(bo);
         // -2 ln u = -2 ln(2) log2(u); v_log_f32 is log2, v_sin/v_cos take revolutions
         const float r = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(ue));
@@ -231,7 +231,7 @@ template <typename R> __device__ __forceinline__ void gauss_pair_scaled(uint32_t
 template <> __device__ __forceinline__ void gauss_pair_scaled<float>(uint32_t be, uint32_t bo, float scale, float &a, float &b)
 {
 #pragma clang fp contract(on)
-    const float ue = ((float)be + 0.5f) * 0x1p-21f;
+    const float ue = __builtin_fmaf((float)be, 0x1p-21f, 0x1p-22f);
     const float uo = turn21(bo);
     const float r = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(ue)) * scale;
     a = r * __builtin_amdgcn_cosf(uo);
