@@ -593,7 +593,7 @@ lb_status set_node_tiles(lb_handle *h, int which, int ns, int ty)
 // in FP32 and two otherwise (us per step, one replica, FP32: 128^2 4 x 16 rows 2.6, 2 x 6 2.9,
 // 1 x 4 4.0; 256^2 4 x 16 3.8, 2 x 10 3.4, 2 x 16 4.0, 1 x 4 4.2; FP64: 64^2 4 x 14 4.8, 2 x 6 3.6, 1 x 4
 // 4.8, 256^2 2 x 10 5.1, 1 x 4 5.3).  Beyond, the tallest tiles of which a CU holds two workgroups: 16
-// rows in FP32 (60 VGPRs; 1500 x 1101: 2 x 16 21.3, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.5, 13.3 and
+// rows in FP32 (58 VGPRs; 1500 x 1101: 2 x 16 21.1, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.2, 13.3 and
 // 13.5), 12 in FP64 (80 VGPRs; 2048 x 400: 2 x 12 23.6, 2 x 16 28.4, 1 x 4 25.1; 512^2 11.4, 11.7, 11.4).
 void node_tile_shape(const lb_handle *h, int *ns, int *ty)
 {
@@ -749,7 +749,7 @@ void radial_metric(int nx, int ny, int *P, int *xwide, int *nbins)
 // as strips those widths, without a kernel of fixed width, ran 20-40% slower at every size), with tiles of
 // 32, 16 and 64 rows, and for each width the tile heights whose workgroup lists just fill 1, 2, 3, 4 or 6
 // rounds of the workgroups resident at once (a launch whose last round is partly empty leaves CUs idle
-// while it drains; at 8192^2 and 256 lanes, 89-row tiles, three rounds: 2% faster than 32-row ones; at
+// while it drains; at 8192^2 and 256 lanes, 95-row tiles, three rounds: 1.3-2% faster than 32-row ones; at
 // 2048^2 19-row tiles, one round: 49.6-51.4 us per step, 18 rows, two workgroups over a round, 61.3, 10
 // rows 54.6, 24 rows 56.5).
 std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
@@ -763,16 +763,17 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
     for (const auto &d : h->reps) max_ny = std::max(max_ny, d.ny);
     const bool plain = h->precision == LB_FP32, cn = !h->cn_reps.empty();
     // Near-ties go to the earlier candidate.  For a population buffer of more than 1 GiB the
-    // heights that just fill whole rounds of resident workgroups come first (at 8192^2 the 67- and
-    // 89-row tiles run about 1% faster than 32-row ones in the kernel trace, within the tuner's
+    // heights that just fill whole rounds of resident workgroups come first (at 8192^2 the 95- and
+    // 47-row tiles run 1.5-2% faster than 32-row ones in the kernel trace, about the tuner's
     // margin); for smaller states 32, 16 and 64 rows come first: their trials read an input that
     // the 256 MB last-level cache partly holds from the trial before, which ranks the shapes
     // differently from the running lattice (the ensemble's 512 x 64 tiles: 0.126 ms per step in
     // the trials against 512 x 32's 0.128, 0.131 against 0.127 when stepping)
     const bool fill_first = (double)h->L.nodes * 9 * elem_size(h->precision) > (double)(1ll << 30);
-    // and for those large states the 256-lane strips come first: over 600 steps of the 8192^2
-    // lattice on one MI355X, 256 x 67 and 256 x 32 tiles ran 0.630 and 0.631 ms per step, every
-    // 512-lane shape 0.638-0.657, while the short trials ranked 512 x 92 within 1% of them
+    // and for those large states the 256-lane strips come first: at 8192^2 on one MI355X 256 x 95 and
+    // 256 x 47 tiles take 0.591 ms per step in the longer trials, 256 x 32 0.600, the best 512-lane shape
+    // 0.604 (over 600 steps, with strips of bx - 6 columns, 0.630 for 256 lanes and 0.638-0.657 for 512,
+    // while the short trials had put 512 x 92 within 1%)
     std::vector<int> widths = fill_first ? std::vector<int>{256, 512} : std::vector<int>{512, 256};
     for (int bx : {384, 448})
         if (std::any_of(h->reps.begin(), h->reps.end(), [bx](const RepDesc &d) { return d.nx > 256 && d.nx <= bx; }))
@@ -909,8 +910,8 @@ lb_status autotune(lb_handle *h)
     // near-ties resolve the same way on every device (LBF_TUNE_LOG prints the timings).  The
     // margin also covers what these ~40 ms trials miss: they run 3-4% faster than the sustained
     // rate, and more so for short tiles, whose recomputed halo rows cost more at the lower clock
-    // of a long run (8192^2: 256 x 16 two-step tiles 0.6147 ms per step in the trial, 0.6415 over
-    // 600 steps; 256 x 67 0.6200 and 0.6290).  Trial
+    // of a long run (8192^2, strips of 250 columns: 256 x 16 two-step tiles 0.6147 ms per step in the
+    // trial, 0.6415 over 600 steps; 256 x 67 0.6200 and 0.6290).  Trial
     // length: at least ~10 ms of steps, from the first candidate's time per step; ms is the time
     // per step.
     int trial = 4;
