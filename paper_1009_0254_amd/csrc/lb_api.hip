@@ -1326,18 +1326,29 @@ lb_status lb_set_sampling(lb_handle *h, int64_t every, int64_t first_step)
     return LB_OK;
 }
 
+// The event that a synchronous call's last kernel completes, or null for a wait on the stream: where no
+// event could be made, and on a stream under capture, which has to refuse the wait (a captured launch
+// completes no event, so a wait for it would return at once with old values).
+static hipEvent_t own_event(const lb_handle *h)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const bool plain = hipStreamIsCapturing(h->stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+    return plain ? h->done : nullptr;
+}
+
 lb_status lb_moments(lb_handle *h, int32_t rep, double *d_m9, double *h_totals)
 {
     if (!h || rep < 0 || rep >= h->n_rep) return LB_EINVAL;
     const RepDesc &d = h->reps[rep];
     const long long n = (long long)d.nx * d.ny;
     const int nb = (int)std::min<long long>(MAX_RED_BLOCKS, (n + 255) / 256);
-    const bool host_sum = h->pinned && h->done;
+    const hipEvent_t done = own_event(h);
+    const bool host_sum = h->pinned && done;
     if (launch_moments(h->precision, h->fbuf[h->par], h->reps_d, d, rep, d_m9, host_sum ? h->pinned : h->partials, nb,
-                       host_sum ? nullptr : h->tot, host_sum ? h->done : nullptr, h->stream) != hipSuccess)
+                       host_sum ? nullptr : h->tot, host_sum ? done : nullptr, h->stream) != hipSuccess)
         return LB_EDEVICE;
     if (host_sum) {
-        if (hipEventSynchronize(h->done) != hipSuccess) return LB_EDEVICE;
+        if (hipEventSynchronize(done) != hipSuccess) return LB_EDEVICE;
         if (h_totals) reduce_partials(h->pinned, nb, h_totals);
         return LB_OK;
     }
@@ -1388,10 +1399,11 @@ lb_status lb_structure_factor(lb_handle *h, int32_t op, int32_t rep, double *out
         if (rep < 0 || !out) return LB_EINVAL;
         const RepDesc &d = h->reps[rep];
         const double inv = h->nsamples[rep] > 0 ? 1.0 / (double)h->nsamples[rep] : 0.0;
-        if (launch_sk_read(h->acc + h->acc_off[rep], out, d.nx, d.ny, inv, h->done, h->stream) != hipSuccess)
+        const hipEvent_t done = own_event(h);
+        if (launch_sk_read(h->acc + h->acc_off[rep], out, d.nx, d.ny, inv, done, h->stream) != hipSuccess)
             return LB_EDEVICE;
         if (nsamples) *nsamples = h->nsamples[rep];
-        return hip_ok(h->done ? hipEventSynchronize(h->done) : hipStreamSynchronize(h->stream));
+        return hip_ok(done ? hipEventSynchronize(done) : hipStreamSynchronize(h->stream));
     }
     case LB_SK_SNAPSHOT: {
         if (rep < 0) return LB_EINVAL;
