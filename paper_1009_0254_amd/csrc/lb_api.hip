@@ -59,14 +59,16 @@ namespace {
 
 // Pinned host memory for the partial sums of lb_moments (48 KB a handle): the kernel writes them there and
 // the host adds them up after the kernel, instead of a second kernel and a copy to unpinned memory (one
-// step and the moments of a 72 x 50 lattice: 35 -> 26 us).  A block costs ~0.26 ms to allocate, so those of
-// freed handles are kept, at most PINNED_KEPT of them, for handles that follow.
+// step and the moments of a 72 x 50 lattice: 35 -> 26 us).  A block costs 40 to 260 us to allocate, so those of
+// freed handles are kept, at most PINNED_KEPT of them, for handles that follow, and a handle's first call
+// makes do without (sums on the device) when none is kept: only a second call allocates.
 constexpr size_t PINNED_DOUBLES = 6 * 1024;
 constexpr int PINNED_KEPT = 16;
 std::mutex g_pinned_mu;
 std::vector<double *> g_pinned;
 
-double *pinned_take()
+// a kept block, or a new one if `allocate`, or null
+double *pinned_take(bool allocate)
 {
     {
         std::lock_guard<std::mutex> lock(g_pinned_mu);
@@ -76,6 +78,7 @@ double *pinned_take()
             return p;
         }
     }
+    if (!allocate) return nullptr;
     void *p = nullptr;
     if (hipHostMalloc(&p, PINNED_DOUBLES * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
         return (double *)p;
@@ -354,7 +357,8 @@ struct lb_handle {
     unsigned long long *tdev = nullptr;
     unsigned *flags = nullptr;
     double *partials = nullptr, *tot = nullptr, *rho_tmp = nullptr;
-    double *pinned = nullptr;        // host memory for lb_moments' partial sums (nullptr: none to be had)
+    double *pinned = nullptr;        // host memory for lb_moments' partial sums (nullptr: not taken, or none to be had)
+    int pinned_asked = 0;            // calls that looked for it: the second may allocate, later ones do not look
     hipEvent_t done = nullptr;       // completed by the last kernel of a synchronous call
     ~lb_handle();
     hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -1135,8 +1139,7 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
         delete h;
         return st;
     }
-    // without either, lb_moments sums on the device and calls wait for the stream
-    h->pinned = pinned_take();
+    // without it calls wait for the stream, and lb_moments sums on the device
     if (hipEventCreate(&h->done) != hipSuccess) {
         h->done = nullptr;
         (void)hipGetLastError();
@@ -1343,6 +1346,7 @@ lb_status lb_moments(lb_handle *h, int32_t rep, double *d_m9, double *h_totals)
     const long long n = (long long)d.nx * d.ny;
     const int nb = (int)std::min<long long>(MAX_RED_BLOCKS, (n + 255) / 256);
     const hipEvent_t done = own_event(h);
+    if (done && !h->pinned && h->pinned_asked < 2) h->pinned = pinned_take(h->pinned_asked++ > 0);
     const bool host_sum = h->pinned && done;
     if (launch_moments(h->precision, h->fbuf[h->par], h->reps_d, d, rep, d_m9, host_sum ? h->pinned : h->partials, nb,
                        host_sum ? nullptr : h->tot, host_sum ? done : nullptr, h->stream) != hipSuccess)
