@@ -89,12 +89,13 @@ __host__ __device__ inline double div64(double a, double v)
 #endif
 }
 
-// sqrt(x) for finite x >= 0 (0 gives 0; below the normal range, where the root is under 1.5e-154,
-// only its size is kept), NaN for a NaN
+// sqrt(x) for finite x >= 0, NaN for a NaN and for +infinity.  The clamp, at the smallest positive double,
+// keeps the estimate finite for x = 0 only; below the normal range the residual of the last line rounds
+// away and what is left is Newton's step from the estimate, within 2^-44
 __host__ __device__ inline double sqrt64(double x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const double y = __builtin_amdgcn_rsq(fmax(x, 0x1p-1022));
+    const double y = __builtin_amdgcn_rsq(fmax(x, 0x1p-1074));
     double g = x * y;
     const double h = 0.5 * y;
     g = fma(fma(-h, g, 0.5), g, g);
