@@ -823,9 +823,9 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
 int step2_one_round_rows(const lb_handle *h)
 {
     constexpr int bx = 256;
-    const int w = step2_out(bx, (int)elem_size(h->precision));
     if (h->n_rep != 1 || h->L.nodes < 5ll << 19) return 0;
-    const int nx = h->reps[0].nx, ny = h->reps[0].ny, strips = (nx + w - 1) / w;
+    const int nx = h->reps[0].nx, ny = h->reps[0].ny;
+    const int w = step2_out(bx, (int)elem_size(h->precision), nx), strips = (nx + w - 1) / w;
     if (nx <= bx || 5ll * nx < 4ll * strips * w) return 0;
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

@@ -17,7 +17,7 @@
 //     pulls from the neighbouring columns of the first step's output): the first step is
 //     valid at lanes 1 .. BG - 2, the second step's densities at 2 .. BG - 3 and its results
 //     at 3 .. BG - 4.  So strips overlap by six columns or a few more and store columns [x0, x0 +
-//     step2_out(BG)).
+//     step2_out).
 // The group marches down the rows.  Stage 1 (step t) collides row r; its output row goes to
 // LDS (populations 1, 3, 5, 6, 7, 8, which the pull of step t + 1 takes from the next
 // column) and registers (0, 2, 4, which stay in the column).  Stage 2 (step t + 1) pulls row
@@ -133,7 +133,8 @@ __global__ void __launch_bounds__(512) k_step2(const S *__restrict__ xi, long lo
     const bool xtra = whole && (l == 0 || l == nx - 1);
     const unsigned xslot = l == 0 ? nx + 1 : 0;
     // stage 2 stores lanes whose column is one of the tile's output columns
-    const bool store2 = whole ? l < nx : (l >= 3 && l < 3 + (unsigned)step2_out((int)BG, ES) && (unsigned)(tl.x0 - 3 + (int)l) < nx);
+    const bool store2 = whole ? l < nx : (l >= 3 && l < 3 + (unsigned)step2_out((int)BG, ES, (int)nx) &&
+                                          (unsigned)(tl.x0 - 3 + (int)l) < nx);
 
     // periodic row index; v is at most a few rows outside [0, ny) (more than one period only
     // for lattices a few rows tall), so the wrap is a short uniform loop, not a division

@@ -119,7 +119,7 @@ static int groups_for(int nx, int bx)
 }
 
 // The two-step kernel's work list.  Strips of a replica wider than a workgroup overlap by six
-// columns or a few more (each stores step2_out(bx)); whole rows of narrower replicas are packed G to a workgroup,
+// columns or a few more (each stores step2_out columns); whole rows of narrower replicas are packed G to a workgroup,
 // G vertically adjacent tiles of one replica (they share boundary rows), with empty groups
 // (rep = -1) after the last tile of a replica.  XCD placement as in make_tiles: a replica
 // with at least 8 strips is split into 8 contiguous strip groups, one per XCD queue; smaller
@@ -142,7 +142,7 @@ int make_tiles2(const std::vector<RepDesc> &reps, int elem, int bx, double h, st
         const RepDesc &d = reps[r];
         const Bands B(d.ny, h);
         if (d.nx > bx) {
-            const int w2 = step2_out(bx, elem);
+            const int w2 = step2_out(bx, elem, d.nx);
             const int ns = (d.nx + w2 - 1) / w2;
             const int parts = ns >= X ? X : 1;
             for (int k = 0; k < parts; ++k) {

@@ -1,0 +1,36 @@
+// Host check of the two-step kernel's strips (make_tiles2): for every width and workgroup size the strips
+// store every column once, their count stays below 17/16 of the fewest possible, and the list fits its bound.
+#include "lb_internal.h"
+
+#include <stdio.h>
+
+using namespace lbf;
+
+int main()
+{
+    long long bad = 0;
+    for (int elem : {4, 8})
+        for (int bx = STEP2_MIN_BX; bx <= 512; bx += 64)
+            for (int nx = 3; nx < 20000; nx += nx < 2100 ? 1 : 7) {
+                RepDesc d{};
+                d.nx = nx;
+                d.ny = STEP2_MIN_H;
+                std::vector<Tile> tiles;
+                std::vector<int32_t> wgs;
+                make_tiles2({d}, elem, bx, STEP2_MIN_H, tiles, wgs);
+                std::vector<int> x0;
+                for (const Tile &t : tiles)
+                    if (t.rep >= 0) x0.push_back(t.x0);
+                const long long n = (long long)x0.size(), w = nx > bx ? step2_out(bx, elem, nx) : nx;
+                const long long fewest = nx > bx ? (nx + bx - 7) / (bx - 6) : 1;
+                bool ok = w <= (nx > bx ? bx - 6 : nx) && n == (nx + w - 1) / w && (n == fewest || 16 * n < 17 * fewest) &&
+                          (long long)tiles.size() <= max_tiles2({nx}, {STEP2_MIN_H});
+                std::vector<char> seen(nx, 0);
+                for (int x : x0)
+                    for (int c = x; c < x + w && c < nx; ++c) ok = ok && !seen[c]++;
+                for (char c : seen) ok = ok && c;
+                if (!ok && bad++ < 10) printf("elem %d bx %d nx %d: %lld strips of %lld (fewest %lld)\n", elem, bx, nx, n, w, fewest);
+            }
+    printf("%lld failures\n", bad);
+    return bad != 0;
+}
