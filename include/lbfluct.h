@@ -209,11 +209,12 @@ lb_status lb_status_flags(lb_handle *h, uint32_t *flags, int64_t *step);
  * second, so that HBM holds only every other state; 4: small lattices in FP32), and that
  * kernel's workgroup (strip) width in lanes, rows per tile and number of workgroups.  The rest of
  * a step count takes single-step launches.  Below 2^22 nodes the configuration follows from the
- * sizes (tiles 64 columns wide with a lane per node, or, for one lattice of 2.6 million nodes or
- * more, strips whose workgroups are all resident at once); for larger ones the configuration is picked by timing candidates on the caller's stream.  The
- * environment variables LBF_TILE="width,rows" (one step per launch) and LBF_TILE2="width,rows"
- * (two) pin a shape of the strips that march down their rows, LBF_STEPS_PER_LAUNCH=1 or 2 their
- * kernel, LBF_NODE_TILE="steps,rows" (1, 2 or 4; at most 16) the tiles with a lane per node.
+ * sizes: tiles 64 columns wide with a lane per node, or, for sets of lattices that keep every
+ * workgroup slot busy (from about 1.6 million nodes on), strips whose workgroups are all resident at
+ * once.  For larger sets it is picked by timing candidates on the caller's stream.  The environment
+ * variables LBF_TILE="width,rows" (one step per launch) and LBF_TILE2="width,rows" (two) pin a
+ * shape of the strips that march down their rows, LBF_STEPS_PER_LAUNCH=1 or 2 their kernel,
+ * LBF_NODE_TILE="steps,rows" (1, 2 or 4; at most 16) the tiles with a lane per node.
  * Handles with correlated noise take one or two steps per launch.  The configuration changes the
  * schedule only: results are bitwise identical for every shape and kernel.
  * Host-only; any output pointer may be NULL. */

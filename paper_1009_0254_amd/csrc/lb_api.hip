@@ -108,7 +108,6 @@ constexpr int CN_MAX = 8192;        // longest side with correlated noise
 // (us per step, 2048 x 400 FP32, 59 MB: 12.5 against 14.2 with the nontemporal policy; 2048^2,
 // 302 MB: one step per launch 65 against 61)
 constexpr size_t TILE_CACHED_BYTES = (size_t)224 << 20;
-constexpr int TILE_ONE_STEP_TY = 4;
 constexpr int SAMPLE_GRAPH_MAX = 256;   // longest sampling interval captured as one graph
 
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
@@ -347,8 +346,8 @@ struct lb_handle {
     Tile *tiles2_d = nullptr;
     int32_t *wgs2_d = nullptr;
     int nwg2 = 0, bx2 = 256, rows2 = 32, gmax2 = 1;
-    // a lane per node (k_tile): tns steps per launch (0: not used), then single steps; the shapes of
-    // the two, their tile counts and tables
+    // a lane per node (k_tile): tns steps per launch (0: k_step2 or k_step), and single steps (no table:
+    // k_step); the shapes of the two, their tile counts and tables
     int tns = 0;
     struct NodeTiles {
         int ns = 1, ty = 4, ntiles = 0;
@@ -576,7 +575,9 @@ lb_status set_node_tiles(lb_handle *h, int which, int ns, int ty)
     lb_handle::NodeTiles &q = h->nt[which];
     q.ns = ns;
     q.ty = ty;
-    q.table = which == 0 ? h->tiles_d : h->tiles2_d;   // lists that k_tile's handles do not use otherwise
+    // the list regions of the one-step and two-step kernels: single steps' takes the first beside k_step2, whose
+    // list fills the second
+    q.table = which == 0 ? h->tiles2_d : h->tiles_d;
     std::vector<Tile> table;
     long long n = 0;
     for (const auto &d : h->reps) {
@@ -590,34 +591,55 @@ lb_status set_node_tiles(lb_handle *h, int which, int ns, int ty)
     return LB_OK;
 }
 
+int compute_units()
+{
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
+        ncu = 256;
+    return ncu;
+}
+
+long long tiles_of(const lb_handle *h, int ns, int ty)
+{
+    long long n = 0;
+    for (const auto &d : h->reps) n += tile_count(d.nx, d.ny, ns, ty);
+    return n;
+}
+
+// Tallest tiles of k_tile's two steps of which a CU holds two workgroups: 16 rows in FP32 (58 VGPRs;
+// 1500 x 1101: 2 x 16 21.1, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.2, 13.3 and 13.5), 12 in FP64 (80 VGPRs;
+// 2048 x 400: 2 x 12 23.6, 2 x 16 28.4, 1 x 4 25.1; 512^2 11.4, 11.7, 11.4).
+int tile_two_rows(const lb_handle *h) { return h->precision == LB_FP64 ? 12 : TILE_MAX_TY; }
+
 // Steps per launch and tile height of k_tile.  A launch costs ~2 us before its first collision,
 // a step inside a launch the collisions of the rows that the tile loses at its edges.  While the
 // tiles of a launch find a CU each, the lost rows cost nothing: the lowest tiles for which that holds
 // are taken (a CU's fewer waves run faster), with four steps per launch for the smallest lattices
 // in FP32 and two otherwise (us per step, one replica, FP32: 128^2 4 x 16 rows 2.6, 2 x 6 2.9,
 // 1 x 4 4.0; 256^2 4 x 16 3.8, 2 x 10 3.4, 2 x 16 4.0, 1 x 4 4.2; FP64: 64^2 4 x 14 4.8, 2 x 6 3.6, 1 x 4
-// 4.8, 256^2 2 x 10 5.1, 1 x 4 5.3).  Beyond, the tallest tiles of which a CU holds two workgroups: 16
-// rows in FP32 (58 VGPRs; 1500 x 1101: 2 x 16 21.1, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.2, 13.3 and
-// 13.5), 12 in FP64 (80 VGPRs; 2048 x 400: 2 x 12 23.6, 2 x 16 28.4, 1 x 4 25.1; 512^2 11.4, 11.7, 11.4).
+// 4.8, 256^2 2 x 10 5.1, 1 x 4 5.3).  Beyond, the tallest useful ones: no lattice of the handle has rows for more
+// (100000 x 3 in tiles of 16 rows, 9 of them idle, 10.3, of 7 rows 7.9).
 void node_tile_shape(const lb_handle *h, int *ns, int *ty)
 {
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
-        ncu = 256;
-    auto count = [&](int s, int y) {
-        long long n = 0;
-        for (const auto &d : h->reps) n += tile_count(d.nx, d.ny, s, y);
-        return n;
-    };
-    const bool fp64 = h->precision == LB_FP64;
+    const int ncu = compute_units();
     *ns = 4;
     *ty = TILE_MAX_TY;
-    if (!fp64 && h->cn_reps.empty() && count(4, TILE_MAX_TY) <= ncu) return;
+    if (h->precision != LB_FP64 && h->cn_reps.empty() && tiles_of(h, 4, TILE_MAX_TY) <= ncu) return;
     *ns = 2;
-    const int most = fp64 ? 12 : TILE_MAX_TY;
+    const int most = std::min(tile_two_rows(h), h->L.max_ny + 4);
     for (*ty = 6; *ty < most; *ty += 2)
-        if (count(2, *ty) <= ncu) return;
+        if (tiles_of(h, 2, *ty) <= ncu) return;
+    *ty = most;
+}
+
+// Rows of k_tile's single steps (the rest of a step count, and calls for one step): 4, or 8 once a CU has
+// 40 tiles to run, where a tile's two more pulled rows weigh more than its waves (us per step, FP32, 4 / 8 rows:
+// 1000^2, 16 tiles a CU, 15.4 / 15.6; 100 x 128^2, 25, 24.0 / 24.7; 1600^2, 39, 31.9 / 31.6; 3 x 1024^2, 48, 39.3 /
+// 38.7; 300 x 12000, 59, 68.5 / 64.0) and has rows for them.
+int tile_one_rows(const lb_handle *h)
+{
+    return h->L.max_ny > 4 && tiles_of(h, 1, 4) > 40ll * compute_units() ? 8 : 4;
 }
 
 // nt[which].ns steps from time t + toff, buffer par into buffer par ^ 1, with the correlated noise in
@@ -646,7 +668,7 @@ hipError_t step_tile(lb_handle *h, int which, int par, int toff, int xi0, hipStr
 }
 
 // `n` steps from buffer *par on stream s, time offsets toff.. (k_tile when tns, else k_step2 for
-// pairs when k = 2); *par follows the state
+// pairs when k = 2, and k_tile or k_step for the rest); *par follows the state
 hipError_t enqueue_steps(lb_handle *h, long long n, int *par, int toff, hipStream_t s)
 {
     long long k = 0;
@@ -678,7 +700,13 @@ hipError_t enqueue_steps(lb_handle *h, long long n, int *par, int toff, hipStrea
             *par ^= 1;
         }
     for (; k < n; ++k) {
-        hipError_t e = step_once(h, *par, toff + (int)k, s);
+        hipError_t e;
+        if (h->nt[1].table) {
+            e = enqueue_noise(h, *par, toff + (int)k, 1, s);
+            if (e == hipSuccess) e = step_tile(h, 1, *par, toff + (int)k, 0, s);
+        } else {
+            e = step_once(h, *par, toff + (int)k, s);
+        }
         if (e != hipSuccess) return e;
         *par ^= 1;
     }
@@ -815,26 +843,57 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
     return shapes;
 }
 
-// Below the sizes that are tuned by timing, one lattice of at least 5/4 2^21 nodes takes the two-step
-// kernel too, in 256-lane strips and the lowest tiles whose workgroups are all resident at once, unless its
-// last strip would leave over a fifth of the strips' columns empty; 0: k_tile.  us per step, k_tile / that:
-// FP32 1450^2 28.5 / 29.1, 1600^2 33.4 / 32.4, 1750^2 39.4 / 34.8, 2000^2 54.9 / 45.0, 300 x 12000 (two
-// strips for 300 columns) 46.8 / 62.1; FP64 1450^2 63.6 / 61.7, 1750^2 89.3 / 78.6, 2000^2 113 / 101.
-int step2_one_round_rows(const lb_handle *h)
+// Below the sizes that are tuned by timing: k_step2 (returns the rows of its tiles and the width) or k_tile (0)?
+// k_step2 marches about rows + 5 iterations, 4.05 us each (5.4 in FP64) when every workgroup that fits the
+// chip is there, and as long with fewer: so the lowest tiles whose workgroups fit at once.  k_tile's time goes
+// with the rows that its tiles pull, 6 more than they store: 16.8 to 18.6 ns a full tile on 256 CUs (27.4).
+// us per step, k_tile / k_step2 in those tiles, FP32: 30 x 256^2 28.5 / 25.4, 56 x 256^2 57.5 / 39.6, 220 x 128^2
+// 66.4 / 40.5, 1000 x 64^2 55.8 / 44.7, 2 x 1400^2 52.3 / 45.6, 1750^2 37.2 / 35.3, 250 x 16000 57.3 / 44.2, 15 x 512^2
+// (512 lanes) 54.3 / 43.7; and where k_tile stays: 2 x 1024^2 27.0 / 31.2, 3 x 1024^2 38.6 / 41.5, 20 x 400^2 39.5 /
+// 41.8, 1450^2 25.6 / 27.7, 1600^2 30.7 / 32.5, 130 x 25000 48.7 / 51.6, 300 x 12000 45.5 / 49.1.  FP64: 1450^2 63.6 /
+// 61.7, 1750^2 89.3 / 78.6, 2000^2 113 / 101.
+int step2_resident_shape(const lb_handle *h, int *width)
 {
-    constexpr int bx = 256;
-    if (h->n_rep != 1 || h->L.nodes < 5ll << 19) return 0;
-    const int nx = h->reps[0].nx, ny = h->reps[0].ny;
-    const int w = step2_out(bx, (int)elem_size(h->precision), nx), strips = (nx + w - 1) / w;
-    if (nx <= bx || 5ll * nx < 4ll * strips * w) return 0;
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    const int slots = ncu * step2_blocks_per_cu(h->precision, h->precision == LB_FP32, !h->cn_reps.empty(), bx, 1);
-    const int bands = slots / strips;
-    if (bands < 1) return 0;
-    return std::max(STEP2_MIN_H, (ny + bands - 1) / bands);
+    const bool fp64 = h->precision == LB_FP64;
+    const int ncu = compute_units(), elem = (int)elem_size(h->precision), hout = tile_two_rows(h) - 4;
+    double tiles = 0;   // in full ones
+    int max_nx = 0;
+    bool fits512 = false;
+    for (const auto &d : h->reps) {
+        const long long bands = (d.ny + hout - 1) / hout;
+        tiles += (double)(tile_count(d.nx, d.ny, 2, hout + 4) / bands) * (double)(d.ny + 6 * bands) / (hout + 6);
+        max_nx = std::max(max_nx, d.nx);
+        fits512 = fits512 || (d.nx > 256 && d.nx <= 512);
+    }
+    double least = (fp64 ? 1.29 : 1.06) * tiles / ncu;   // iterations of k_step2 in k_tile's time
+    if (!h->cn_reps.empty()) least *= 0.9;   // 256 x 8192, 14.1 against 13: 53.4 / 53.8 us with correlated noise
+    int best = 0;
+    if (least <= STEP2_MIN_H + 5) return 0;
+    for (int bx : {max_nx <= 128 ? 128 : 256, 512}) {
+        if (bx == 512 && !fits512) continue;
+        int gmax = 1;
+        for (const auto &d : h->reps)
+            for (int g = 2; g <= bx / 64; g *= 2)
+                if (d.nx <= bx / g) gmax = std::max(gmax, g);
+        const long long slots =
+            (long long)ncu * step2_blocks_per_cu(h->precision, h->precision == LB_FP32, !h->cn_reps.empty(), bx, gmax);
+        if (slots <= 0) continue;
+        int lo = STEP2_MIN_H, hi = std::max(STEP2_MIN_H, h->L.max_ny);   // the lowest that fits, or the tallest
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (step2_workgroups(h->reps, elem, bx, mid) <= slots) hi = mid;
+            else lo = mid + 1;
+        }
+        double its = std::min(lo, h->L.max_ny) + 5;
+        const double rounds = (double)step2_workgroups(h->reps, elem, bx, lo) / (double)slots;
+        if (rounds > 1) its *= 1.05 * rounds;   // lattices of a few long rows: 1000000 x 3 55.1 / 49.7, 400000 x 8 41.7 / 42.1
+        if (its < least) {
+            least = its;
+            best = lo;
+            *width = bx;
+        }
+    }
+    return best;
 }
 
 // time a few steps of each candidate launch shape and keep the fastest: for k_step (one step
@@ -868,22 +927,30 @@ lb_status autotune(lb_handle *h)
     const char *tile_env = getenv("LBF_NODE_TILE");
     const bool pint = tile_env && sscanf(tile_env, "%d,%d", &tns, &tty) == 2;
     const bool small = h->L.nodes < (1ll << 22) && !pin1 && !pin2 && !force_k;
-    const int one_round = small && !pint ? step2_one_round_rows(h) : 0;
-    if (one_round) {
-        lb_status st = set_tiles(h, 256, 8);
-        if (st == LB_OK) st = set_tiles2(h, 256, one_round);
+    int bx0 = 256;
+    while (bx0 > MIN_BX && bx0 / 2 >= min_nx) bx0 /= 2;
+    int bx2 = 256;
+    const int rows2 = small && !pint ? step2_resident_shape(h, &bx2) : 0;
+    if (rows2) {
+        // single steps: k_tile, but k_step where its 256 x 16 tiles just fill the chip once (2 x 2000 x 1000, 1008 of
+        // 1024 slots, 65.0 / 62.8 us; 56 x 256^2, 896, 58.7 / 61.5) or rows leave most of a wave idle (nx 64 59.6 / 65.7,
+        // 30 67.8 / 65.6, 8 233 / 177)
+        long long wgs = 0;
+        for (const auto &d : h->reps) wgs += (long long)((d.nx + bx0 - 1) / bx0) * ((d.ny + 15) / 16);
+        const long long slots = 4ll * compute_units();
+        const bool full = bx0 == 256 && wgs <= slots && 16 * wgs >= 15 * slots;
+        lb_status st = full || max_nx <= 32 ? set_tiles(h, bx0, 16) : set_node_tiles(h, 1, 1, tile_one_rows(h));
+        if (st == LB_OK) st = set_tiles2(h, bx2, rows2);
         h->k = 2;
         return st;
     }
     if (pint || small) {
         if (!pint) node_tile_shape(h, &tns, &tty);
         lb_status st = set_node_tiles(h, 0, tns, tty);
-        if (st == LB_OK) st = set_node_tiles(h, 1, 1, TILE_ONE_STEP_TY);
+        if (st == LB_OK) st = set_node_tiles(h, 1, 1, tile_one_rows(h));
         if (st == LB_OK) h->tns = tns;
         return st;
     }
-    int bx0 = 256;
-    while (bx0 > MIN_BX && bx0 / 2 >= min_nx) bx0 /= 2;
     int bx20 = 256;
     if (max_nx <= 128) bx20 = 128;
     if (pin1 || h->L.nodes < (1ll << 22)) {

@@ -149,6 +149,8 @@ __host__ __device__ constexpr int step2_out(int bx, int elem, int nx)
 // about h rows; returns the largest group count
 int make_tiles2(const std::vector<RepDesc> &reps, int elem, int bx, double h, std::vector<Tile> &tiles,
                 std::vector<int32_t> &wgs);
+// the workgroups of that list
+long long step2_workgroups(const std::vector<RepDesc> &reps, int elem, int bx, double h);
 // upper bound of the tile count of make_tiles2 for any bx >= STEP2_MIN_BX, h >= STEP2_MIN_H
 long long max_tiles2(const std::vector<int> &nx, const std::vector<int> &ny);
 hipError_t launch_step2(int precision, const Step2Launch &a, hipStream_t s);

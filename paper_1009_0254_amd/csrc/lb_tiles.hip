@@ -183,6 +183,22 @@ int make_tiles2(const std::vector<RepDesc> &reps, int elem, int bx, double h, st
     return gmax;
 }
 
+long long step2_workgroups(const std::vector<RepDesc> &reps, int elem, int bx, double h)
+{
+    long long n = 0;
+    for (const RepDesc &d : reps) {
+        const long long bands = Bands(d.ny, h).nt;
+        if (d.nx > bx) {
+            const int w2 = step2_out(bx, elem, d.nx);
+            n += (d.nx + w2 - 1) / w2 * bands;
+        } else {
+            const int G = groups_for(d.nx, bx);
+            n += (bands + G - 1) / G;
+        }
+    }
+    return n;
+}
+
 long long max_tiles2(const std::vector<int> &nx, const std::vector<int> &ny)
 {
     long long t = 0;

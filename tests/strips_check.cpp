@@ -24,7 +24,17 @@ int main()
                 const long long n = (long long)x0.size(), w = nx > bx ? step2_out(bx, elem, nx) : nx;
                 const long long fewest = nx > bx ? (nx + bx - 7) / (bx - 6) : 1;
                 bool ok = w <= (nx > bx ? bx - 6 : nx) && n == (nx + w - 1) / w && (n == fewest || 16 * n < 17 * fewest) &&
-                          (long long)tiles.size() <= max_tiles2({nx}, {STEP2_MIN_H});
+                          (long long)tiles.size() <= max_tiles2({nx}, {STEP2_MIN_H}) &&
+                          (long long)wgs.size() - 1 == step2_workgroups({d}, elem, bx, STEP2_MIN_H);
+                if (nx < 600)   // several bands, several replicas
+                    for (double h : {8.0, 11.0, 40.0}) {
+                        RepDesc e = d, f = d;
+                        e.ny = 8 + nx / 3;
+                        f.nx = 3 + nx / 2;
+                        f.ny = 129;
+                        make_tiles2({d, e, f}, elem, bx, h, tiles, wgs);
+                        ok = ok && (long long)wgs.size() - 1 == step2_workgroups({d, e, f}, elem, bx, h);
+                    }
                 std::vector<char> seen(nx, 0);
                 for (int x : x0)
                     for (int c = x; c < x + w && c < nx; ++c) ok = ok && !seen[c]++;
