@@ -561,15 +561,29 @@ __device__ __forceinline__ long long ceil_root(long long v, long long m)
 // ((2b - 1) P)^2 <= 4 R2 < ((2b + 1) P)^2.  Means over the full k plane without k = 0;
 // the half plane stands for its mirror image with weight 2 except at kx = 0 and nx/2.
 //
-// Two passes, each sum in a fixed order.  k_sk_bins: a block takes SK_BIN_SHELLS adjacent shells and a
+// Each sum in a fixed order.  Large planes whose shells are about as wide as a ky step take two passes.
+// k_sk_bins: a block takes SK_BIN_SHELLS adjacent shells and a
 // range of columns kx, SK_BIN_COLS of them at a time: the lanes of one column hold adjacent shells, whose
 // intervals of ky follow each other, so that they read whole cache lines.  k_sk_bins_sum adds the ranges'
-// partial sums.  With one shell per block each lane's reads were a line of their own: 1.83 ms at 16384^2
-// (1.1 GB), now 0.54 ms.  (A shell per lane walking its columns: 1.64 ms, and 6 times slower than a block
-// per shell at 2048^2, for the lanes whose shell touches the column tangentially.)
-constexpr int SK_BIN_SHELLS = 16, SK_BIN_COLS = 16, SK_SUM_SHELLS = 64, SK_SUM_PARTS = 8;
+// partial sums.  k_sk_bins_one: a block per shell, its lanes over the columns, or where a shell spans many ky
+// (ny > nx: about P = ny / nx of them) LK adjacent lanes over the ky of a column.
+constexpr int SK_BIN_SHELLS = 16, SK_BIN_COLS = 16, SK_SUM_SHELLS = 64, SK_SUM_PARTS = 8, SK_ONE_THREADS = 256;
 // ranges of columns, of one pass each up to 32 ranges
 int sk_bin_ranges(int nh) { return std::min(32, (nh + SK_BIN_COLS - 1) / SK_BIN_COLS); }
+
+// The kernel of an nx x ny plane: LK of k_sk_bins_one, or 0 for the two passes.  us, two passes / LK 1 / 4 / 16:
+// 512^2 10 / 8 / 9 / 21, 1024^2 18 / 14 / 15 / 44, 2048^2 29 / 29 / 32 / 108, 4096^2 59 / 98 / 95 / 355,
+// 8192^2 180 / 384 / 351 / -; wide 4096 x 512 41 / 24 / 43 / 151, 16384 x 1024 174 / 94 / 176 / 651, 8192 x 2048
+// 95 / 98 / 106 / 397, 16384 x 4096 259 / 488 / 364 / -, and of few shells for their columns 8192 x 64 25.7 / 26.8,
+// 16384 x 16 31 / 41; tall 1024 x 2048 30 / 24 / 18 / 43, 2048 x 4096 50 / 72 / 40 / 107, 4096 x 8192 97 / 242 / 116 /
+// 356, 4096 x 16384 338 / 508 / 152 / 354, 512 x 4096 53 / 42 / 25 / 26, 1024 x 16384 249 / 155 / 72 / 73, 256 x 16384
+// 290 / 213 / 91 / 58, 16 x 16384 914 / 699 / 277 / 105.
+int sk_bin_lanes(int nx, int ny, int nbins)
+{
+    const int P = nx >= ny ? nx / ny : ny / nx;
+    if (ny > nx) return P >= 16 ? 16 : P >= 4 || nx <= 2048 ? 4 : 0;
+    return ny >= 2048 || nx / 2 + 1 > 64 * nbins ? 0 : 1;
+}
 
 __global__ void __launch_bounds__(SK_BIN_SHELLS *SK_BIN_COLS)
     k_sk_bins(const double *__restrict__ plane, int nx, int ny, int P, int xwide, int nbins, int cols,
@@ -613,6 +627,50 @@ __global__ void __launch_bounds__(SK_BIN_SHELLS *SK_BIN_COLS)
     if (j == 0 && b < nbins) {
         part[(long long)blockIdx.y * 2 * nbins + b] = ss[0][l];
         part[(long long)blockIdx.y * 2 * nbins + nbins + b] = sc[0][l];
+    }
+}
+
+template <int LK>
+__global__ void __launch_bounds__(SK_ONE_THREADS)
+    k_sk_bins_one(const double *__restrict__ plane, int nx, int ny, int P, int xwide, int nbins, double *__restrict__ out)
+{
+    __shared__ double ss[SK_ONE_THREADS], sc[SK_ONE_THREADS];
+    const int b = blockIdx.x;
+    const long long wx = xwide ? 1 : (long long)P * P, wy = xwide ? (long long)P * P : 1;
+    const long long lo = b > 0 ? (long long)(2 * b - 1) * P * (2 * b - 1) * P : 0;
+    const long long hi = (long long)(2 * b + 1) * P * (2 * b + 1) * P;
+    const int hx = nx / 2, hy = ny / 2;
+    double s = 0, c = 0;
+    for (int kx = threadIdx.x / LK; kx <= hx; kx += SK_ONE_THREADS / LK) {
+        const long long ax = 4 * wx * (long long)kx * kx;
+        if (ax >= hi) break;
+        const int y0 = (int)min(ceil_root(lo - ax, 4 * wy), (long long)hy + 1);
+        const int y1 = (int)min(ceil_root(hi - ax, 4 * wy), (long long)hy + 1);
+        const double w = (kx == 0 || kx == hx) ? 1.0 : 2.0;
+        const double *D = plane + (long long)kx * ny;
+        for (int ky = y0 + (int)threadIdx.x % LK; ky < y1; ky += LK) {
+            if (kx == 0 && ky == 0) continue;
+            s += w * D[ky];
+            c += w;
+            if (ky != 0 && ky != hy) {
+                s += w * D[ny - ky];
+                c += w;
+            }
+        }
+    }
+    ss[threadIdx.x] = s;
+    sc[threadIdx.x] = c;
+    __syncthreads();
+    for (int h = SK_ONE_THREADS / 2; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) {
+            ss[threadIdx.x] += ss[threadIdx.x + h];
+            sc[threadIdx.x] += sc[threadIdx.x + h];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        out[b] = sc[0] > 0 ? ss[0] / sc[0] : 0.0;
+        out[nbins + b] = sc[0];
     }
 }
 
@@ -803,6 +861,13 @@ hipError_t launch_sk_snapshot(int precision, const SkLaunch &a, int nx, int ny, 
     else
         cols_kernel<float, true>(precision, a, 1, plane, s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int lk = sk_bin_lanes(nx, ny, nbins);
+    if (lk) {
+        const auto kernel = lk == 1 ? k_sk_bins_one<1> : lk == 4 ? k_sk_bins_one<4> : k_sk_bins_one<16>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nbins), dim3(SK_ONE_THREADS), 0, s, (const double *)plane, nx, ny, P,
+                           xwide, nbins, out);
+        return hipGetLastError();
+    }
     // the partial sums follow in slot 2: at most nh / 16 + 1 ranges of 2 nbins doubles, nbins <= 0.71 min(nx, ny)
     // + 2 (a slot has ny elements of at least 8 bytes for each of the nh columns, padded to a multiple of 8)
     double *part = (double *)((char *)a.spec + (size_t)sk_elem(precision) * 2 * a.Ptot);
