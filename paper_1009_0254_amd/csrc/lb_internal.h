@@ -241,7 +241,7 @@ struct SkLaunch {
     int32_t lds_cols;         // most column points per block in the range ((cpb + fold) * ny, or ny/2 if split)
     int32_t col_line;         // longest column transform in the range (ny / split)
     int32_t G;                // modes per transform group of the row kernel
-    int64_t Ptot;             // complex elements per mode slot (sum of ny * sk_nh_padded(nx) over all replicas)
+    int64_t Ptot;             // complex elements per mode slot (sum of ny * sk_nh_padded over all replicas)
     void *spec;               // nine mode slots of row spectra (float2 for FP32 storage, else double2)
     double *acc;
     double *base;             // [replica][18]: reference moments (FP64) and populations of the last sample

@@ -394,10 +394,10 @@ __global__ void __launch_bounds__(SK_THREADS)
             const C O = mk2(h * (Zk.y + Zm.y), -h * (Zk.x - Zm.x));
             const C WO = cmul(twiddle(T, k * wstride), O);
             typename V2<Tt>::type *out = spec + (a0 + c) * Ptot + q.soff;
-            out[sk_at(y0 + rr, k, ny)] = cadd(E, WO);
+            out[sk_at<sizeof(C)>(y0 + rr, k, ny)] = cadd(E, WO);
             if (2 * k != M) {
                 const C D = csub(E, WO);
-                out[sk_at(y0 + rr, M - k, ny)] = mk2(D.x, -D.y);
+                out[sk_at<sizeof(C)>(y0 + rr, M - k, ny)] = mk2(D.x, -D.y);
             }
         };
         const int lh = logM - 1;   // M/2 = 2^lh
@@ -468,7 +468,7 @@ __global__ void __launch_bounds__(SK_THREADS)
                 C v[4];
                 for (int u = 0; u < 4; ++u) {
                     const int e = min(e0 + u * (int)blockDim.x, (n4 << logL) - 1);
-                    v[u] = S0[sk_at32((e >> 2) & (L - 1), kx0 + (e >> (2 + logL)) * 4 + (e & 3), ny)];
+                    v[u] = S0[sk_at32<sizeof(C)>((e >> 2) & (L - 1), kx0 + (e >> (2 + logL)) * 4 + (e & 3), ny)];
                 }
                 for (int u = 0; u < 4; ++u) {
                     const int e = e0 + u * (int)blockDim.x, y = (e >> 2) & (L - 1);
@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(SK_THREADS)
                 C v[4];
                 for (int u = 0; u < 4; ++u) {
                     const int e = min(e0 + u * (int)blockDim.x, tot - 1);
-                    v[u] = S0[sk_at32(sk_fill_y(e & (L - 1), logL), kx0 + (e >> logL), ny)];
+                    v[u] = S0[sk_at32<sizeof(C)>(sk_fill_y(e & (L - 1), logL), kx0 + (e >> logL), ny)];
                 }
                 for (int u = 0; u < 4; ++u) {
                     const int e = e0 + u * (int)blockDim.x;
@@ -497,7 +497,7 @@ __global__ void __launch_bounds__(SK_THREADS)
                 for (int u = 0; u < 4; ++u) {
                     const int e = min(e0 + u * (int)blockDim.x, tot - 1), y = e >> lCp;
                     const int c = min(e & ((1 << lCp) - 1), C_ - 1);
-                    v[u] = S0[sk_at(y, kx0 + c, ny)];
+                    v[u] = S0[sk_at<sizeof(C)>(y, kx0 + c, ny)];
                 }
                 for (int u = 0; u < 4; ++u) {
                     const int e = e0 + u * (int)blockDim.x, y = e >> lCp, c = e & ((1 << lCp) - 1);
@@ -510,7 +510,7 @@ __global__ void __launch_bounds__(SK_THREADS)
         const int wstride = nmax / ny;
         for (int r = threadIdx.x; r < L; r += blockDim.x) {
             const int n = P16 ? sk_fill_y(r, logL) : r;
-            const C u = S0[sk_at32(n, kx0, ny)], v = S0[sk_at32(n + L, kx0, ny)];
+            const C u = S0[sk_at32<sizeof(C)>(n, kx0, ny)], v = S0[sk_at32<sizeof(C)>(n + L, kx0, ny)];
             X[lds_at((int)bitrev((unsigned)n, logL), sh)] =
                 par == 0 ? cadd(u, v) : cmul(csub(u, v), twiddle(T, n * wstride));
         }
