@@ -31,6 +31,8 @@
  *     or aborts.  Errors leave the handle usable unless stated otherwise.
  *   - Device memory and the stream belong to the caller.  The library never calls
  *     hipMalloc: it carves the caller's workspace.  The workspace must outlive the handle.
+ *     Held until the process ends: 768 KB of pinned host memory, taken by its first lb_init
+ *     and shared by the handles' lb_moments, and a device array (see lb_moments_static).
  *   - Functions enqueue work on the stream given to lb_init and return without
  *     waiting, except where marked "synchronous".
  *   - A handle must not be used from two host threads at once.

@@ -57,46 +57,50 @@ lb_status static_scratch_of(int *device, double **out)
 
 namespace {
 
-// Pinned host memory for the partial sums of lb_moments (48 KB a handle): the kernel writes them there and
-// the host adds them up after the kernel, instead of a second kernel and a copy to unpinned memory (one
-// step and the moments of a 72 x 50 lattice: 35 -> 26 us).  A block costs 40 to 260 us to allocate, so those of
-// freed handles are kept, at most PINNED_KEPT of them, for handles that follow, and a handle's first call
-// makes do without (sums on the device) when none is kept: only a second call allocates.
+// Pinned host memory for the partial sums of lb_moments: the kernel writes them there and the host adds them
+// up after the kernel, instead of a second kernel and a copy to unpinned memory (one step and the moments of a
+// 72 x 50 lattice: 35 -> 26 us).  Allocating costs 40 to 260 us and is not allowed while a stream is being captured,
+// so the process' first lb_init takes PINNED_SLOTS blocks of 48 KB at once, which are held until the process ends.
+// A handle has one from lb_init to lb_free, or none while others have them all: its sums stay on the device.
 constexpr size_t PINNED_DOUBLES = 6 * 1024;
-constexpr int PINNED_KEPT = 16;
-std::mutex g_pinned_mu;
-std::vector<double *> g_pinned;
+constexpr int PINNED_SLOTS = 16;
+struct Pinned {
+    std::mutex mu;
+    double *base = nullptr;
+    bool asked = false, used[PINNED_SLOTS] = {};
+};
+Pinned g_pinned;
 
-// a kept block, or a new one if `allocate`, or null
-double *pinned_take(bool allocate)
+double *pinned_take()
 {
-    {
-        std::lock_guard<std::mutex> lock(g_pinned_mu);
-        if (!g_pinned.empty()) {
-            double *p = g_pinned.back();
-            g_pinned.pop_back();
-            return p;
-        }
+    std::lock_guard<std::mutex> lock(g_pinned.mu);
+    if (!g_pinned.asked) {
+        g_pinned.asked = true;
+        // another thread's capture is no concern of this allocation
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, PINNED_SLOTS * PINNED_DOUBLES * sizeof(double),
+                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess)
+            g_pinned.base = (double *)p;
+        else
+            (void)hipGetLastError();   // not an error of the launches that follow
+        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
-    if (!allocate) return nullptr;
-    void *p = nullptr;
-    if (hipHostMalloc(&p, PINNED_DOUBLES * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-        return (double *)p;
-    (void)hipGetLastError();   // not an error of the launches that follow
+    if (g_pinned.base)
+        for (int k = 0; k < PINNED_SLOTS; ++k)
+            if (!g_pinned.used[k]) {
+                g_pinned.used[k] = true;
+                return g_pinned.base + k * PINNED_DOUBLES;
+            }
     return nullptr;
 }
 
 void pinned_give(double *p)
 {
     if (!p) return;
-    {
-        std::lock_guard<std::mutex> lock(g_pinned_mu);
-        if ((int)g_pinned.size() < PINNED_KEPT) {
-            g_pinned.push_back(p);
-            return;
-        }
-    }
-    (void)hipHostFree(p);
+    std::lock_guard<std::mutex> lock(g_pinned.mu);
+    g_pinned.used[(p - g_pinned.base) / PINNED_DOUBLES] = false;
 }
 
 constexpr size_t ALIGN = 256;
@@ -356,8 +360,7 @@ struct lb_handle {
     unsigned long long *tdev = nullptr;
     unsigned *flags = nullptr;
     double *partials = nullptr, *tot = nullptr, *rho_tmp = nullptr;
-    double *pinned = nullptr;        // host memory for lb_moments' partial sums (nullptr: not taken, or none to be had)
-    int pinned_asked = 0;            // calls that looked for it: the second may allocate, later ones do not look
+    double *pinned = nullptr;        // host memory for lb_moments' partial sums (nullptr: none to be had)
     hipEvent_t done = nullptr;       // completed by the last kernel of a synchronous call
     ~lb_handle();
     hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -1206,11 +1209,12 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
         delete h;
         return st;
     }
-    // without it calls wait for the stream, and lb_moments sums on the device
+    // without them calls wait for the stream, and lb_moments sums on the device
     if (hipEventCreate(&h->done) != hipSuccess) {
         h->done = nullptr;
         (void)hipGetLastError();
     }
+    h->pinned = pinned_take();
     h->n_rep = n_rep;
     h->precision = precision;
     h->features = features;
@@ -1413,7 +1417,6 @@ lb_status lb_moments(lb_handle *h, int32_t rep, double *d_m9, double *h_totals)
     const long long n = (long long)d.nx * d.ny;
     const int nb = (int)std::min<long long>(MAX_RED_BLOCKS, (n + 255) / 256);
     const hipEvent_t done = own_event(h);
-    if (done && !h->pinned && h->pinned_asked < 2) h->pinned = pinned_take(h->pinned_asked++ > 0);
     const bool host_sum = h->pinned && done;
     if (launch_moments(h->precision, h->fbuf[h->par], h->reps_d, d, rep, d_m9, host_sum ? h->pinned : h->partials, nb,
                        host_sum ? nullptr : h->tot, host_sum ? done : nullptr, h->stream) != hipSuccess)
