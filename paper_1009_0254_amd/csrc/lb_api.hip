@@ -1301,7 +1301,6 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
         h->acc = (double *)(h->ws + L.acc);
         h->sk_base = (double *)(h->ws + L.sk_base);
         long long rows = 0, cols = 0, soff = 0;
-        int max_col = 0, max_row = 0;
         const int row_div = sk_divisor(n_rep, SK_MIN_ROW_BLOCKS, [&](int r, int div, bool *more) -> long long {
             const int rpb = std::max(1, sk_rows_per_block(p[r].nx, p[r].ny) / div);
             *more = *more || rpb > 1;
@@ -1329,17 +1328,15 @@ lb_status lb_init(const lb_params *p, int32_t n_rep, int32_t precision, uint32_t
             q.soff = soff;
             q.acc_off = (int64_t)h->acc_off[r];
             rows += (q.ny + q.rpb - 1) / q.rpb;
-            max_row = std::max(max_row, q.rpb * q.nx);
             cols += sk_col_blocks(nh, q.cpb, q.split, q.fold);
             soff += (long long)q.ny * sk_nh_padded(q.nx, sk_elem(precision));
-            max_col = std::max(max_col, (q.cpb + q.fold) * (q.ny / q.split));
             h->sk.push_back(q);
         }
         h->sk_rows = rows;
         h->sk_cols = cols;
         e = hipMemcpyAsync(h->sk_d, h->sk.data(), sizeof(SkRep) * n_rep, hipMemcpyHostToDevice, h->stream);
         if (e == hipSuccess) e = launch_twiddles(h->sk_tw, L.sk_nmax, h->stream);
-        if (e == hipSuccess) e = set_sk_lds_limits(precision, L.sk_G, max_row, max_col);
+        if (e == hipSuccess) e = set_sk_lds_limits(precision);
         if (e == hipSuccess) e = launch_fill(h->acc, (int64_t)L.acc_elems, 0.0, h->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) {

@@ -254,7 +254,7 @@ int sk_elem(int precision);
 int sk_modes_per_pass(int precision, int max_nx);
 int sk_split(int precision, int ny);
 int sk_cols_per_block(int precision, int nx, int ny);
-hipError_t set_sk_lds_limits(int precision, int G, int max_row, int max_col);
+hipError_t set_sk_lds_limits(int precision);
 // add |m_a(k)|^2 / n, a = 0..8, of every replica in the range to its accumulators
 hipError_t launch_sk_sample(int precision, const SkLaunch &a, hipStream_t s);
 // |rho(k)|^2 / n of replica a.r0 (a one-replica range), radially binned into out[0..nbins)

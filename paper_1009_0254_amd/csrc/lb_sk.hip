@@ -831,10 +831,13 @@ int sk_cols_per_block(int precision, int nx, int ny)
     return ny >= pts ? 1 : std::min(pts / ny, nx / 2);   // a power of two
 }
 
-hipError_t set_sk_lds_limits(int precision, int G, int max_row, int max_col)
+// The most that any handle's blocks take (the limit belongs to the kernel, in the whole process): the long
+// rows' budget, and half of the longest column (shorter whole ones fit COL_BUDGET)
+hipError_t set_sk_lds_limits(int precision)
 {
-    const size_t rows = (size_t)sk_elem(precision) * lds_padded((long long)G * (max_row / 2)),
-                 cols = sk_col_lds_bytes(precision, max_col);
+    const int elem = sk_elem(precision);
+    const size_t rows = (size_t)elem * lds_padded(ROW_BUDGET_LONG / elem),
+                 cols = sk_col_lds_bytes(precision, std::max(COL_BUDGET / elem, SK_MAX / 2));
     return precision == 0 ? lds_limits_of<double, double>(rows, cols) : lds_limits_of<float, float>(rows, cols);
 }
 
