@@ -571,9 +571,8 @@ hipError_t step_pair(lb_handle *h, int par, int toff, hipStream_t s)
 // k_tile's launch of ns steps in tiles of ty rows: nt[0] (tns steps) or nt[1] (single steps)
 lb_status set_node_tiles(lb_handle *h, int which, int ns, int ty)
 {
-    // what k_tile's variants, launch bounds and tile geometry allow
-    if (!(ns == 1 || ns == 2 || (ns == 4 && h->precision != LB_FP64 && h->cn_reps.empty())) || ty <= 4 * (ns - 1) ||
-        ty > TILE_MAX_TY)
+    // what launch_tile takes
+    if (!tile_has_kernel(h->precision, ns, !h->cn_reps.empty()) || ty <= 4 * (ns - 1) || ty > TILE_MAX_TY)
         return LB_EINVAL;
     lb_handle::NodeTiles &q = h->nt[which];
     q.ns = ns;

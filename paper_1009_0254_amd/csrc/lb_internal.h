@@ -179,8 +179,11 @@ struct TileLaunch {
     int32_t plain, cached;
 };
 constexpr int TILE_MAX_TY = 16;
+// steps per launch that there is a kernel for
+bool tile_has_kernel(int precision, int ns, bool correlated);
+// hipErrorInvalidValue for a launch without a kernel, or of tiles without a row to store or over TILE_MAX_TY rows
 hipError_t launch_tile(int precision, const TileLaunch &a, hipStream_t s);
-// LDS of a workgroup: at most 42 KB (FP32) or 84 KB (FP64)
+// LDS of a workgroup: at most 36.6 KB (FP32) or 73.3 KB (FP64)
 size_t tile_lds_bytes(int precision, int ns, int ty);
 // tiles of a replica
 long long tile_count(int nx, int ny, int ns, int ty);

@@ -279,8 +279,15 @@ template <typename S, typename R, bool PLAIN> static void launch_tile_ns(const T
         launch_tile_t<S, R, PLAIN, false, 4>(a, s);
 }
 
+bool tile_has_kernel(int precision, int ns, bool correlated)
+{
+    return ns == 1 || ns == 2 || (ns == 4 && precision != 0 && !correlated);
+}
+
 hipError_t launch_tile(int precision, const TileLaunch &a, hipStream_t s)
 {
+    if (!tile_has_kernel(precision, a.ns, a.xi != nullptr) || a.ty <= 4 * (a.ns - 1) || a.ty > TILE_MAX_TY)
+        return hipErrorInvalidValue;
     if (precision == 0)
         launch_tile_ns<double, double, false>(a, s);
     else if (a.plain)
