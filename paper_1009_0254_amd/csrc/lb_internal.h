@@ -133,17 +133,18 @@ struct Step2Launch {
 constexpr int STEP2_MIN_BX = 128, STEP2_MIN_H = 8;
 // Columns that a strip of bx lanes stores: bx - 6 at most.  In FP32 from 256 lanes on a multiple of 64 bytes where
 // rows are one too (nx a multiple of 16), so that neighbouring strips, which reach a row at different times, share no
-// 64-byte line of it, unless that takes a sixteenth more strips or over.  us per step of the best shapes, 250 or 506
-// columns / 240 or 496: 8192^2 630 / 621, 16000 x 3000 470 / 454, 4096^2 169.7 / 167.9; with a sixteenth more
-// 8000 x 4000 309.4 / 306.6, 4000^2 161.2 / 166.6; with more 2496 x 2500 65.7 / 74.2, 1008 x 8000 84.1 / 95.7; rows of
-// no such multiple 1000 x 8000 85.2 / 94.7, 1500 x 6000 95.3 / 101.4.  FP64, not bound by memory, gains nothing
-// (8192^2 without noise 1060 / 1058) and takes a strip more.  Narrower strips keep bx - 6: 10 of 122 columns would be
-// lost.
-__host__ __device__ constexpr int step2_out(int bx, int elem, int nx)
+// 64-byte line of it, if that takes no more strips, or, for lattices beyond the last-level cache, less than a sixteenth
+// more.  us per step of the best shapes, 250 or 506 columns / 240 or 496: 8192^2 630 / 621, 16000 x 3000 470 / 454,
+// 4096^2 169.7 / 167.9; with a sixteenth more 8000 x 4000 309.4 / 306.6, 4000^2 161.2 / 166.6; with more
+// 2496 x 2500 65.7 / 74.2, 1008 x 8000 84.1 / 95.7; a lattice in the cache 1000000 x 3 47.5 / 49.9; rows of no such
+// multiple 1000 x 8000 85.2 / 94.7, 1500 x 6000 95.3 / 101.4.  FP64, not bound by memory, gains nothing (8192^2 without
+// noise 1060 / 1058) and takes a strip more.  Narrower strips keep bx - 6: 10 of 122 columns would be lost.
+__host__ __device__ constexpr int step2_out(int bx, int elem, int nx, int ny)
 {
     const int full = bx - 6, even = full / 16 * 16;
-    return bx >= 256 && elem == 4 && nx % 16 == 0 && 16 * ((nx + even - 1) / even) < 17 * ((nx + full - 1) / full) ? even
-                                                                                                                    : full;
+    if (bx < 256 || elem != 4 || nx % 16 != 0) return full;
+    const int nf = (nx + full - 1) / full, ne = (nx + even - 1) / even;
+    return ne == nf || (16 * ne < 17 * nf && (long long)nx * ny >= 1ll << 22) ? even : full;
 }
 // tiles and workgroup prefix of the two-step kernel for workgroups of bx lanes and tiles of
 // about h rows; returns the largest group count

@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(512) k_step2(const S *__restrict__ xi, long lo
     const bool xtra = whole && (l == 0 || l == nx - 1);
     const unsigned xslot = l == 0 ? nx + 1 : 0;
     // stage 2 stores lanes whose column is one of the tile's output columns
-    const bool store2 = whole ? l < nx : (l >= 3 && l < 3 + (unsigned)step2_out((int)BG, ES, (int)nx) &&
+    const bool store2 = whole ? l < nx : (l >= 3 && l < 3 + (unsigned)step2_out((int)BG, ES, (int)nx, (int)ny) &&
                                           (unsigned)(tl.x0 - 3 + (int)l) < nx);
 
     // periodic row index; v is at most a few rows outside [0, ny) (more than one period only

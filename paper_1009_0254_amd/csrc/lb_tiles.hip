@@ -142,7 +142,7 @@ int make_tiles2(const std::vector<RepDesc> &reps, int elem, int bx, double h, st
         const RepDesc &d = reps[r];
         const Bands B(d.ny, h);
         if (d.nx > bx) {
-            const int w2 = step2_out(bx, elem, d.nx);
+            const int w2 = step2_out(bx, elem, d.nx, d.ny);
             const int ns = (d.nx + w2 - 1) / w2;
             const int parts = ns >= X ? X : 1;
             for (int k = 0; k < parts; ++k) {
@@ -189,7 +189,7 @@ long long step2_workgroups(const std::vector<RepDesc> &reps, int elem, int bx, d
     for (const RepDesc &d : reps) {
         const long long bands = Bands(d.ny, h).nt;
         if (d.nx > bx) {
-            const int w2 = step2_out(bx, elem, d.nx);
+            const int w2 = step2_out(bx, elem, d.nx, d.ny);
             n += (d.nx + w2 - 1) / w2 * bands;
         } else {
             const int G = groups_for(d.nx, bx);

@@ -11,22 +11,23 @@ int main()
     long long bad = 0;
     for (int elem : {4, 8})
         for (int bx = STEP2_MIN_BX; bx <= 512; bx += 64)
-            for (int nx = 3; nx < 20000; nx += nx < 2100 ? 1 : 7) {
+            for (int nx = 3, ny = STEP2_MIN_H; nx < 20000; nx += ny > STEP2_MIN_H ? (nx < 2100 ? 1 : 7) : 0,
+                     ny = ny > STEP2_MIN_H ? STEP2_MIN_H : 1 << 15) {
                 RepDesc d{};
                 d.nx = nx;
-                d.ny = STEP2_MIN_H;
+                d.ny = ny;
                 std::vector<Tile> tiles;
                 std::vector<int32_t> wgs;
-                make_tiles2({d}, elem, bx, STEP2_MIN_H, tiles, wgs);
+                make_tiles2({d}, elem, bx, ny, tiles, wgs);   // one band
                 std::vector<int> x0;
                 for (const Tile &t : tiles)
                     if (t.rep >= 0) x0.push_back(t.x0);
-                const long long n = (long long)x0.size(), w = nx > bx ? step2_out(bx, elem, nx) : nx;
+                const long long n = (long long)x0.size(), w = nx > bx ? step2_out(bx, elem, nx, ny) : nx;
                 const long long fewest = nx > bx ? (nx + bx - 7) / (bx - 6) : 1;
-                bool ok = w <= (nx > bx ? bx - 6 : nx) && n == (nx + w - 1) / w && (n == fewest || 16 * n < 17 * fewest) &&
-                          (long long)tiles.size() <= max_tiles2({nx}, {STEP2_MIN_H}) &&
-                          (long long)wgs.size() - 1 == step2_workgroups({d}, elem, bx, STEP2_MIN_H);
-                if (nx < 600)   // several bands, several replicas
+                bool ok = w <= (nx > bx ? bx - 6 : nx) && n == (nx + w - 1) / w && (n == fewest || (16 * n < 17 * fewest && (long long)nx * ny >= 1 << 22)) &&
+                          (long long)tiles.size() <= max_tiles2({nx}, {ny}) &&
+                          (long long)wgs.size() - 1 == step2_workgroups({d}, elem, bx, ny);
+                if (nx < 600 && ny == STEP2_MIN_H)   // several bands, several replicas
                     for (double h : {8.0, 11.0, 40.0}) {
                         RepDesc e = d, f = d;
                         e.ny = 8 + nx / 3;
