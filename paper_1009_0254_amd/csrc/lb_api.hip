@@ -609,7 +609,7 @@ long long tiles_of(const lb_handle *h, int ns, int ty)
     return n;
 }
 
-// Tallest tiles of k_tile's two steps of which a CU holds two workgroups: 16 rows in FP32 (58 VGPRs;
+// Tallest tiles of k_tile's two steps of which a CU holds two workgroups: 16 rows in FP32 (56 VGPRs;
 // 1500 x 1101: 2 x 16 21.1, 2 x 12 24.7, 1 x 4 22.9; 2048 x 400 12.2, 13.3 and 13.5), 12 in FP64 (80 VGPRs;
 // 2048 x 400: 2 x 12 23.6, 2 x 16 28.4, 1 x 4 25.1; 512^2 11.4, 11.7, 11.4).
 int tile_two_rows(const lb_handle *h) { return h->precision == LB_FP64 ? 12 : TILE_MAX_TY; }
@@ -1104,7 +1104,7 @@ lb_status capture_graph(lb_handle *h, int par)
     }
     int p = par;
     if (enqueue_steps(h, GRAPH_STEPS, &p, 0, cs) != hipSuccess) st = LB_EDEVICE;
-    if (p != par) st = LB_EDEVICE;   // an even number of launches of 1, 2 or 4 steps: the state returns to buffer par
+    if (p != par) st = LB_EDEVICE;   // 32, 16 or 8 launches: the state returns to buffer par
     if (launch_advance_time(h->tdev, GRAPH_STEPS, cs) != hipSuccess) st = LB_EDEVICE;
     if (hipStreamEndCapture(cs, &g) != hipSuccess) st = LB_EDEVICE;
     if (st == LB_OK && hipGraphInstantiate(&h->graph[par], g, nullptr, nullptr, 0) != hipSuccess) st = LB_EDEVICE;

@@ -161,9 +161,9 @@ int step2_blocks_per_cu(int precision, bool plain, bool cn, int bx, int max_grou
 // allow k_step2 the dynamic LDS of its largest configuration (512 lanes in 8 groups)
 hipError_t set_step2_lds_limit();
 
-// Small and middle-sized lattices (lb_tile.hip): ns steps per launch (1, 2 or, in FP32
-// without correlated noise, 4), a lane per node, tiles of 64 columns and ty rows (the first step's; a step
-// more loses two at each edge).  table[r].x0 is the index of replica r's first tile (unused for
+// Small and middle-sized lattices (lb_tile.hip), and single steps beside k_step2 of larger ones: ns steps per
+// launch (1, 2 or, in FP32 without correlated noise, 4), a lane per node, tiles of 64 columns and ty rows (the
+// first step's; a step more loses two at each edge).  table[r].x0 is the index of replica r's first tile (unused for
 // one replica); cached: 0 stores with the nontemporal policy.
 struct TileLaunch {
     const void *xi;
@@ -229,7 +229,7 @@ struct SkRep {
     int32_t rpb;        // rows per row block (a power of two)
     int32_t logrpb;     // log2(rpb)
     int64_t row0;       // first row block of this replica (prefix of ceil(ny / rpb))
-    int64_t col0;       // first column block (prefix of split * ceil(nh / cpb)), nh = nx/2 + 1
+    int64_t col0;       // first column block (prefix of sk_col_blocks), nh = nx/2 + 1
     int64_t soff;       // offset (complex elements) of its spectrum (sk_at layout) inside one mode slot
     int64_t acc_off;    // offset (double) of its [9][nh][ny] accumulators
 };

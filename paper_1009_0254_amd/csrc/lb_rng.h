@@ -77,7 +77,7 @@ __host__ __device__ inline double rcp64(double v)
 #endif
 }
 
-// a / v for finite a and normal v whose quotient is normal
+// a / v for a = 0 or |a| of 2^-900 to 2^900 and normal v whose quotient is normal
 __host__ __device__ inline double div64(double a, double v)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -90,7 +90,7 @@ __host__ __device__ inline double div64(double a, double v)
 #endif
 }
 
-// sqrt(x) for finite x >= 0, NaN for a NaN and for +infinity.  The clamp, at the smallest positive double,
+// sqrt(x) for finite x >= 0, NaN for a NaN and for +infinity (where the populations are not finite either).  The clamp, at the smallest positive double,
 // keeps the estimate finite for x = 0 only; below the normal range the residual of the last line rounds
 // away and what is left is Newton's step from the estimate, within 2^-44
 __host__ __device__ inline double sqrt64(double x)

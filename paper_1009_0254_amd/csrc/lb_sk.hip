@@ -3,17 +3,18 @@
 // (Sec. III notation).  For a real field |a(k)|^2 = |a(-k)|^2, so the transforms below
 // use exp(-2 pi i k x / n) and keep the half plane kx = 0..nx/2.
 //
-// A sample covers a range of replicas of any sizes with two launches, whatever their sizes:
-//   1. rows: one workgroup per lattice row of any replica in the range.  It pulls the
-//      pre-collision populations, forms the nine moments relative to those of a reference
-//      (the mean pulled populations of row 0, from a one-block-per-replica pre-pass) in the
+// A sample covers a range of replicas of any sizes with two launches, after a third for the reference
+// (k_sk_ref, one block per replica) unless the row blocks are few enough to form it themselves:
+//   1. rows: a workgroup takes one lattice row of any replica in the range, or several narrow ones
+//      while the launch still fills the chip.  It pulls the pre-collision populations, forms the nine
+//      moments relative to those of the reference (the mean pulled populations of row 0) in the
 //      transform precision (FP32 for FP32 storage, FP64 for FP64 storage) and turns
 //      each real row of length nx into its half spectrum with one complex transform of
 //      length nx/2 (even samples as real part, odd as imaginary, then the standard split),
-//      G modes at a time in LDS until all nine are done (for FP32 rows up to 8192 the
-//      moments stay in registers between groups; otherwise each group pulls again and the
-//      repeats hit the caches), writing mode a to slot a of the spectra, [ny][nx/2+1] each;
-//   2. columns: one workgroup per kx and mode reads its column of the row spectra in place
+//      G modes at a time in LDS until all nine are done (for FP32 rows up to 8192 of launches that
+//      fill the chip the moments stay in registers between groups; otherwise each group pulls again
+//      and the repeats hit the caches), writing mode a to slot a of the spectra (lb_sklayout.h);
+//   2. columns: a workgroup takes one mode and a few adjacent kx, or one kx of a long column, in place
 //      (consecutive kx share cache lines and are kept on one XCD), transforms along y
 //      (a column longer than 64 KiB of LDS is split by one decimation-in-frequency stage
 //      into two half-length transforms, one per output parity, so that it fits), restores
@@ -26,7 +27,7 @@
 // The transforms are lb_fftcore.h's radix-8 passes (radix 4 for the FP64 columns).
 // The radially binned density spectrum (the isotropic average of S_rho(k), used to follow
 // density modes after a quench to c_s^2 < 0, where M(k) of eq. (lb-lang-ft) has growing
-// eigenvalues) reuses 1-3 for mode 0 of one replica and bins |rho(k)|^2 / n with integer
+// eigenvalues) reuses them for mode 0 of one replica and bins |rho(k)|^2 / n with integer
 // shell arithmetic.
 
 #include <hip/hip_ext.h>
@@ -114,7 +115,8 @@ template <typename U> __device__ __forceinline__ void moments9(const U g[9], U m
 constexpr int SK_CACHE_PAIRS = 4;   // node pairs per lane whose moments stay in registers
 
 // Two adjacent stored values, one load: half the requests of the row kernels, whose lanes hold node pairs
-// (one sample, 8192^2: 3.85 -> 3.59 ms, 4096^2 1.08 -> 0.97 ms, 2048^2 FP64 415 -> 391 us; aligned to one value only: x - 1 and x + 1 are odd)
+// (one sample, 8192^2: 3.85 -> 3.59 ms, 4096^2 1.08 -> 0.97 ms, 2048^2 FP64 415 -> 391 us).  Aligned to one
+// value only: x - 1 and x + 1 are odd.
 template <typename S> struct __attribute__((packed, aligned(sizeof(S)))) SkTwo {
     S a, b;
 };
@@ -288,9 +290,9 @@ __global__ void __launch_bounds__(SK_REF_THREADS)
 // SK_CACHE_PAIRS) are pulled once and their nine moments kept in registers for all mode
 // groups, which are GC modes each and fixed at compile time (so that a placed group's
 // registers are free for the transforms); otherwise each group of G modes pulls the row
-// again (the repeats hit L2 or the MALL; GC = 1: mode 0 alone, for the snapshot).  OWNREF: every block forms its replica's reference itself
-// (blocks of SK_REF_THREADS lanes; the same sums in the same order) instead of reading k_sk_ref's,
-// and the replica's first block stores it for the column pass.
+// again (the repeats hit L2 or the MALL; GC = 1: mode 0 alone, for the snapshot).  OWNREF: every block
+// forms its replica's reference itself (blocks of SK_REF_THREADS lanes; the same sums in the same
+// order) instead of reading k_sk_ref's, and the replica's first block stores it for the column pass.
 template <typename S, typename Tt, int RMAX, bool CACHE, int GC, bool OWNREF = false>
 __global__ void __launch_bounds__(SK_THREADS)
     k_sk_rows(const S *__restrict__ f, const RepDesc *__restrict__ reps, const SkRep *__restrict__ sk, int r0, int r1,

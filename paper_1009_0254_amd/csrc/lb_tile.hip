@@ -18,7 +18,7 @@
 //
 // What bounds it: below ~2^17 nodes the chain of a launch (~2 us to the first collision, then 1.5 us
 // a step in FP32, 3 us in FP64: the collision's own dependent instructions); from ~2^19 nodes VALU
-// issue, the lost rows included (2048 x 400 in FP32: 25 us for 9.2 M wave instructions per two
+// issue, the lost rows included (2048 x 400 in FP32: 24.4 us for 10.3 M wave instructions per two
 // steps).  Measured, us per step, k_step2's 16-row tiles before and these after: 64^2 FP64 41 / 3.6,
 // 128^2 FP32 24 / 2.6, 512^2 FP32 23.6 / 6.0, 2048 x 400 FP32 24.8 / 12.2, FP64 45 / 23.6,
 // 1500 x 1101 FP32 30.6 / 21.1.
@@ -35,7 +35,7 @@ constexpr int DW = TX + 2;    // slots of a density row
 // CACHED: stores go through the caches (the next step's reads find them there) instead of carrying
 // the nontemporal policy.
 // Waves per SIMD: with the launch bound alone the compiler aims at one workgroup of 1024 and parks values
-// in the accumulation registers; asked for 8 (6 in FP64) it fits 54 to 58 vector registers without them, 18
+// in the accumulation registers; asked for 8 (6 in FP64) it fits 54 to 56 vector registers without them, 18
 // instructions less per node (2048 x 400 12.55 -> 12.18 us per step, 1500 x 1101 21.38 -> 21.10).
 template <typename S, typename R, bool PLAIN, bool CN, int NS, bool CACHED>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 6 : 8)))
