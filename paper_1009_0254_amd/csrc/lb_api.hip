@@ -847,7 +847,7 @@ std::vector<std::pair<int, int>> step2_shapes(const lb_handle *h)
 
 // Below the sizes that are tuned by timing: k_step2 (returns the rows of its tiles and the width) or k_tile (0)?
 // k_step2 marches about rows + 5 iterations, 4.05 us each (5.4 in FP64) when every workgroup that fits the
-// chip is there, and as long with fewer: so the lowest tiles whose workgroups fit at once.  k_tile's time goes
+// chip is there (2.3 us with a quarter of them): so the lowest tiles whose workgroups fit at once.  k_tile's time goes
 // with the rows that its tiles pull, 6 more than they store: 16.8 to 18.6 ns a full tile on 256 CUs (27.4).
 // us per step, k_tile / k_step2 in those tiles, FP32: 30 x 256^2 28.5 / 25.4, 56 x 256^2 57.5 / 39.6, 220 x 128^2
 // 66.4 / 40.5, 1000 x 64^2 55.8 / 44.7, 2 x 1400^2 52.3 / 45.6, 1750^2 37.2 / 35.3, 250 x 16000 57.3 / 44.2, 15 x 512^2
